@@ -50,6 +50,33 @@ __device__ __forceinline__ uint64_t ld_relaxed64(const uint64_t* p) {
 __device__ __forceinline__ void st_relaxed64(uint64_t* p, uint64_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// XCD-local signal: a store through to the XCD's L2 (workgroup scope: the L1 is
+// write-through) and a load served by that L2.  The vector L1 has no instruction that
+// bypasses or drops it short of the agent-scope invalidate, so the load goes through the
+// scalar data cache, invalidated first (s_dcache_inv; the invalidate has to finish before
+// the load is issued).  Only for words that one XCD's workgroups alone store and load
+// during a kernel: the value reaches memory, and other XCDs, with a writeback or the
+// kernel's end.  One way between two CUs of an XCD it takes 541-566 shader clocks wherever
+// the line lives, an agent-scope store and poll 970-1780 (2000 hand-overs, two idle
+// workgroups).  `p` must be the same for the whole wavefront (uniform_ptr).
+__device__ __forceinline__ void st_xcd64(uint64_t* p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ uint64_t ld_xcd64(const uint64_t* p) {
+  uint64_t v;
+  __asm__ __volatile__(
+      "s_dcache_inv\n\ts_waitcnt lgkmcnt(0)\n\ts_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)"
+      : "=&s"(v) : "s"(p) : "memory");
+  return v;
+}
+// A pointer that is the same for the whole wavefront, in scalar registers.
+template <class T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
+}
 __device__ __forceinline__ uint32_t add_relaxed(uint32_t* p, uint32_t v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

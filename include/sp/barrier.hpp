@@ -258,15 +258,6 @@ struct XcdLocal {
   uint32_t groups, copies, sstride, fenced, poll_sleep, lanes;
 };
 
-// A pointer that is the same for the whole workgroup, in scalar registers.
-template <class T>
-__device__ __forceinline__ T* uniform_ptr(T* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
-}
-
 // The master's stores of its stamp: copy c at pub[c] + the XCD's index in xmail.
 constexpr uint32_t kMaxCopies = 256;
 
