@@ -77,14 +77,27 @@ __device__ __forceinline__ T* uniform_ptr(T* p) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
 }
+// For a read-modify-write whose address is the same in every lane the compiler first
+// combines the lanes' operands and then spreads the returned value over them, which waits
+// for the value at once.  Only a leader lane issues these, so there is nothing to combine,
+// and the wait would keep the caller from doing anything while the value is on its way:
+// a pointer in vector registers, of which the compiler knows nothing, is left alone.
+template <class T>
+using global_ptr = __attribute__((address_space(1))) T*;
+template <class T>
+__device__ __forceinline__ global_ptr<T> lane_ptr(T* p) {
+  global_ptr<T> g = (global_ptr<T>)p;
+  __asm__("" : "+v"(g));
+  return g;
+}
 __device__ __forceinline__ uint32_t add_relaxed(uint32_t* p, uint32_t v) {
-  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_fetch_add(lane_ptr(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint32_t exch_relaxed(uint32_t* p, uint32_t v) {
   return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint32_t max_relaxed(uint32_t* p, uint32_t v) {
-  return __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_fetch_max(lane_ptr(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Compare-and-swap; returns the value seen (== expected on success).
 __device__ __forceinline__ uint32_t cas_relaxed(uint32_t* p, uint32_t expected, uint32_t desired) {
@@ -146,6 +159,13 @@ __device__ __forceinline__ uint32_t xcc_id() {
 // Identity of the CU within its XCD: HW_REG_HW_ID bits [15:8] (CU, SH and SE ids).
 __device__ __forceinline__ uint32_t cu_in_xcc() {
   return (__builtin_amdgcn_s_getreg((31 << 11) | (0 << 6) | 4) >> 8) & 0xFF;
+}
+
+// A value (the same for the whole wavefront) that is computed where this stands: the
+// compiler otherwise moves arithmetic down to its use, into a critical section.
+__device__ __forceinline__ uint32_t computed_here(uint32_t v) {
+  __asm__ __volatile__("" : "+s"(v));
+  return v;
 }
 
 // Busy-wait `cycles` shader clocks (non-critical delays and critical-section holds).

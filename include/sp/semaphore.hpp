@@ -89,10 +89,10 @@ __device__ __forceinline__ uint32_t xchain_units(const SemState& s, uint32_t x) 
 
 // ---- array semaphore (ticket-indexed grant slots); 64-bit counters of the slot kinds ----
 __device__ __forceinline__ uint64_t add_relaxed64(uint64_t* p, uint64_t v) {
-  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_fetch_add(lane_ptr(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint64_t max_relaxed64(uint64_t* p, uint64_t v) {
-  return __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_fetch_max(lane_ptr(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint64_t* as_tickets(const SemState& s) {
   return reinterpret_cast<uint64_t*>(cq_base(s, 0));
@@ -115,6 +115,7 @@ __device__ __forceinline__ uint64_t* chain_slots(const SemState& s, uint32_t x, 
   const uint32_t n = i + units < m ? i + units : i + units - m;
   uint32_t* slots = cq_base(s, x) + 2 * (size_t)s.cq_stride;
   *next = reinterpret_cast<uint64_t*>(slots + (size_t)n * s.cq_stride);
+  __asm__ __volatile__("" : "+v"(*next));  // found here, not where the post uses it
   return reinterpret_cast<uint64_t*>(slots + (size_t)i * s.cq_stride);
 }
 

@@ -49,8 +49,8 @@ constexpr uint32_t kCohortSlots = 4096;
 // first add is in flight while the holder holds, and each workgroup keeps the maximum it
 // has seen and raises the shared one once, at its end: a pair adds two atomics to the
 // tracker's words instead of three and waits for one instead of two.
-// 2048 workgroups, K = 32, 2^18 tracked pairs: 16.4 ms against 17.1; 257 workgroups, K = 4, 2^14 pairs
-// with the pool: 11.8 ms against 12.8.
+// 2048 workgroups, K = 32, 2^18 tracked pairs: 16.4 ms against 17.1; 257 workgroups, K = 4,
+// 2^14 pairs with the pool: 11.8 ms against 12.8.
 template <int KIND, bool FENCED>
 __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_t* state, uint32_t nwg,
                       uint64_t total, uint32_t max_hold, uint32_t seed, uint32_t track,
@@ -63,12 +63,15 @@ __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_
   uint32_t* occ = state + L_OCC * stride;
   uint32_t* maxocc = state + L_MAXOCC * stride;
   const bool pool = data && s.K > 1;
+  const uint32_t last = sp::computed_here(blockDim.x - 1);  // a load from the dispatch packet
   uint32_t c = 0, most = 0;
   uint64_t j = 0;
   sp::SemHold sh{0};  // the adaptive kind's learned post interval, kept across waits
   for (; j < A; ++j) {
-    const uint32_t hold = sp::sched_key(seed, b, (uint32_t)j, 3) % (max_hold + 1);
-    const uint32_t first = pool ? sp::sched_key(seed, b, (uint32_t)j, 4) % s.K : 0;
+    const uint32_t hold =
+        sp::computed_here(sp::sched_key(seed, b, (uint32_t)j, 3) % (max_hold + 1));
+    const uint32_t first =
+        pool ? sp::computed_here(sp::sched_key(seed, b, (uint32_t)j, 4) % s.K) : 0;
     if (!(pool ? sp::sem_wait<KIND, false>(s, ctl, &sh) : sp::sem_wait<KIND, FENCED>(s, ctl, &sh)))
       break;
     uint32_t inside = 0;
@@ -96,7 +99,7 @@ __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_
       slot = s_slot;
       if (slot >= s.K) break;  // the watchdog ended the run
     }
-    if (data && threadIdx.x == blockDim.x - 1) {
+    if (data && threadIdx.x == last) {
       if constexpr (FENCED) data[slot] = data[slot] + 1;
       else sp::st_relaxed(data + slot, sp::ld_relaxed(data + slot) + 1);
     }
