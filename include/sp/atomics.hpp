@@ -44,6 +44,14 @@ __device__ __forceinline__ uint32_t ld_cu(const uint32_t* p) {
 __device__ __forceinline__ void st_cu(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+// Four words of one 16-byte aligned block at workgroup scope, in one access.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x4 ld_cu128(const uint32_t* p) {
+  u32x4 v;
+  __asm__ __volatile__("global_load_dwordx4 %0, %1, off sc0\n\ts_waitcnt vmcnt(0)"
+                       : "=v"(v) : "v"(p) : "memory");
+  return v;
+}
 __device__ __forceinline__ uint64_t ld_relaxed64(const uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -69,13 +77,18 @@ __device__ __forceinline__ uint64_t ld_xcd64(const uint64_t* p) {
       : "=&s"(v) : "s"(p) : "memory");
   return v;
 }
+// A value that one lane (the leader) loaded, in a scalar register: a loop on it then
+// branches as one, without the exec-mask arithmetic of a loop that lanes may leave apart.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) {
+  return __builtin_amdgcn_readfirstlane(v);
+}
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+  return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
+}
 // A pointer that is the same for the whole wavefront, in scalar registers.
 template <class T>
 __device__ __forceinline__ T* uniform_ptr(T* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
+  return reinterpret_cast<T*>(uniform(reinterpret_cast<uint64_t>(p)));
 }
 // For a read-modify-write whose address is the same in every lane the compiler first
 // combines the lanes' operands and then spreads the returned value over them, which waits
@@ -213,7 +226,7 @@ struct Wait {
   __device__ __forceinline__ bool tick() {
     sleep_units(poll_sleep);
     if ((++n & 63) != 0) return true;
-    if (ld_relaxed(ctl.err) != DEV_OK) return false;
+    if (uniform(ld_relaxed(ctl.err)) != DEV_OK) return false;
     if (wall_clock() > ctl.deadline) {
       cas_relaxed(ctl.err, DEV_OK, DEV_TIMEOUT);
       return false;

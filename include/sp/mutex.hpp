@@ -23,7 +23,8 @@ struct MutexState {
                           // holders of one CU in a row
   BackoffCfg bo;        // backoff between failed attempts
   uint32_t* cuq;        // CU cohort: per lock, XCC id and CU id, kCuLines lines (CU ticket,
-                        // CU grant, session record), qstride (>= 4) words apart
+                        // CU grant and session record, completions), qstride (>= 4) words
+                        // apart
 };
 
 // What the leader remembers about a lock it holds: for the ticket mutex, the ticket it
@@ -39,6 +40,9 @@ struct MutexHold {
   uint32_t cu_ticket;   // SP_MUTEX_CU_COHORT: the ticket drawn on this CU
   uint32_t cu_session;  // SP_MUTEX_CU_COHORT: holders of this CU before this one since the
                         // CU's cohort took the XCD lock (0 = this holder took it)
+  uint32_t cu_pass;     // SP_MUTEX_CU_COHORT: at entry, a later CU ticket was announced and
+                        // the CU's session may grow
+  uint32_t* cu;         // SP_MUTEX_CU_COHORT: the grant line of the holder's CU
 };
 
 // Cohort lock state of `lock` for the XCD with XCC id x (kXccSlots per lock: the XCC id
@@ -64,13 +68,15 @@ __device__ __forceinline__ uint64_t* cohort_grant(const MutexState& s, uint32_t 
 }
 
 // CU cohort state of `lock` for the CU with id c (HW_ID bits [15:8], kCuIds values) on the
-// XCD with XCC id x: line 0 the CU's ticket counter, line 1 its grant word (CU turn, bits
-// 0-23, modulo 2^24 | CU session, bits 24-31), line 2 the record of the XCD cohort lock
-// the CU's session holds (words 0-2: local ticket, session, global ticket) and in word 3
-// the count of CU tickets drawn as some waiter last announced it (a lower bound: racing
-// announcements may land out of order).  Grant, record and announcement are stored and
-// loaded at workgroup scope: only workgroups of that CU touch them, and they share the
-// CU's L1, in which a store by one wavefront is seen by the others.
+// XCD with XCC id x: line 0 the CU's ticket counter; line 1, read in one 16-byte access,
+// word 0 the grant (CU turn, bits 0-23, modulo 2^24 | CU session, bits 24-31), word 1 the
+// count of CU tickets drawn as some waiter last announced it (a lower bound: racing
+// announcements may land out of order), words 2-3 the record of the XCD cohort lock the
+// CU's session holds (local ticket, bits 0-23 | session, bits 24-31; global ticket); line
+// 2 the holders whose critical sections' stores have completed into the L2, and every
+// earlier holder's too.  Lines 1 and 2 are stored and loaded at workgroup scope: only
+// workgroups of that CU touch them, and they share the CU's L1, in which a store by one
+// wavefront is seen by the others.
 constexpr uint32_t kCuIds = 256;
 constexpr uint32_t kCuLines = 3;
 __device__ __forceinline__ uint32_t* cu_line(const MutexState& s, uint32_t lock, uint32_t x,
@@ -80,6 +86,11 @@ __device__ __forceinline__ uint32_t* cu_line(const MutexState& s, uint32_t lock,
 
 namespace detail {
 
+// A ticket beyond t has been drawn (both modulo 2^24, as the grants count them).
+__device__ __forceinline__ bool drawn_after(uint32_t drawn, uint32_t t) {
+  return (int32_t)((drawn - (t + 1)) << 8) > 0;
+}
+
 // The XCD cohort lock's two levels, shared by SP_MUTEX_COHORT and SP_MUTEX_CU_COHORT:
 // take XCD x's local ticket, wait for its grant, and queue for the global lock when the
 // grant says the XCD's cohort does not hold it.  Leader only.
@@ -88,11 +99,11 @@ __device__ __forceinline__ bool cohort_acquire(const MutexState& s, uint32_t loc
                                                uint32_t* g) {
   bool ok = true;
   *t = add_relaxed(cohort_ticket(s, lock, x), 1);
-  const uint64_t* grant = cohort_grant(s, lock, x, *t);
+  const uint64_t* grant = uniform_ptr(cohort_grant(s, lock, x, *t));
   uint64_t v;
   for (;;) {
-    v = ld_relaxed64(grant);
-    if (((uint32_t)v & kTurnMask) == (*t & kTurnMask)) break;
+    v = ld_xcd64(grant);  // written on this XCD
+    if (((uint32_t)v & kTurnMask) == (uniform(*t) & kTurnMask)) break;
     if (!(ok = w.tick())) break;
   }
   *k = ((uint32_t)v >> 24) & 0xFF;
@@ -100,7 +111,7 @@ __device__ __forceinline__ bool cohort_acquire(const MutexState& s, uint32_t loc
   if (ok && *k == 0) {  // the cohort does not hold the global lock: queue for it
     *g = add_relaxed(s.ticket + (size_t)lock * s.stride, 1);
     const uint32_t* turn = s.turn + (size_t)lock * s.stride;
-    while (ld_relaxed(turn) != *g)
+    while (uniform(ld_relaxed(turn)) != uniform(*g))
       if (!(ok = w.tick())) break;
   }
   return ok;
@@ -116,16 +127,16 @@ __device__ __forceinline__ void cohort_release(const MutexState& s, uint32_t loc
                                                uint32_t g) {
   uint64_t* grant = cohort_grant(s, lock, x, t + 1);  // the next local ticket's slot
   const uint64_t next_turn = (t + 1) & kTurnMask;
-  if ((int32_t)(drawn - (t + 1)) > 0 && k < s.cohort_bound) {
+  if (drawn_after(drawn, t) && k < s.cohort_bound) {
     // The next holder runs on this XCD: pass the global lock with the local one.  The
     // critical section's stores have completed into this XCD's L2, which the next holder
     // reads through after its own acquire: no writeback.
-    st_relaxed64(grant, ((uint64_t)g << 32) | ((uint64_t)k << 24) | next_turn);
+    st_xcd64(grant, ((uint64_t)g << 32) | ((uint64_t)k << 24) | next_turn);
   } else {
     uint32_t* turn = s.turn + (size_t)lock * s.stride;
     if constexpr (FENCED) st_release(turn, g + 1);  // writes back every local holder's stores
     else st_relaxed(turn, g + 1);
-    st_relaxed64(grant, next_turn);  // session 0: the next local holder queues globally
+    st_xcd64(grant, next_turn);  // session 0: the next local holder queues globally
   }
 }
 
@@ -166,21 +177,33 @@ __device__ __forceinline__ uint32_t* mcs_node(const MutexState& s, uint32_t lock
 //                         ticket's slot: turn + 1, session k + 1) when a local ticket beyond
 //                         one's own was drawn and k + 1 < cohort_bound; that hand-over
 //                         needs no L2 writeback, since both holders use this XCD's L2
-//                         (the critical section's stores have completed into it).
+//                         (the critical section's stores have completed into it), and
+//                         neither do the grants: they pass through that L2 (st_xcd64 /
+//                         ld_xcd64).  One lock, 16 words, 256 workgroups: 1.01 M
+//                         acquisitions/s, from 0.79 with agent-scope grants; 16 locks,
+//                         2048 workgroups: 16.7 from 13.0.
 //                         Otherwise it releases the global lock (with the writeback), then
 //                         grants the local turn with session 0.  Cohorts are the actual
 //                         XCDs (XCC id), never merged: the local hand-over relies on the
 //                         shared L2.
 //   SP_MUTEX_CU_COHORT    CU-cohort lock: SP_MUTEX_COHORT behind a ticket lock per CU.  A
-//                         waiter draws a CU ticket, announces it in the CU's record line
-//                         and polls the CU's grant word at workgroup scope (in the CU's
-//                         L1).  Session k > 0: the CU's cohort holds the XCD lock (the
-//                         record says how), enter with no cache maintenance, since the
-//                         previous holder's stores went through this L1.  Session 0: take
-//                         the XCD-cohort lock, acquire, write the record.  Unlock passes
-//                         within the CU (session k + 1) when a later CU ticket was
-//                         announced and k + 1 < cohort_bound, else hands the XCD lock on
-//                         and grants session 0.
+//                         waiter draws a CU ticket, announces it in the CU's grant line
+//                         and polls that line at workgroup scope (in the CU's L1), grant,
+//                         announcement and session record in one access.  Session k > 0:
+//                         the CU's cohort holds the XCD lock (the record says how), enter
+//                         with no cache maintenance, since the previous holder's stores
+//                         went through this L1.  Session 0: take the XCD-cohort lock,
+//                         acquire, write the record.  Unlock passes within the CU (session
+//                         k + 1) when a later CU ticket was announced and k + 1 <
+//                         cohort_bound, else hands the XCD lock on and grants session 0.
+//                         What bounds a hand-over within the CU is two trips to the L2,
+//                         the grant's and the data's (a store leaves no copy in the L1 to
+//                         hit), and the workgroup's barriers: grant to poll ~0.25 us, poll
+//                         to critical section 0.12, the section 0.15, section to grant 0.1
+//                         (2048 workgroups on one lock).  So nothing else stands between:
+//                         no wait for the stores (mutex_unlock), no load of the record.
+//                         One lock, 16 words, 2048 workgroups: 1.54 M acquisitions/s, from
+//                         1.14 with the stores awaited and the record loaded apart.
 //   SP_MUTEX_MCS          MCS queue lock: each workgroup has a node per lock (next, locked)
 //                         in its own line; lock stores next = none and locked = 1, then
 //                         exchanges the lock word (the queue's tail) with its node id;
@@ -207,6 +230,7 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
                            MutexHold* hold = nullptr) {
   __shared__ uint32_t s_ok;
   if (is_leader()) {
+    s_ok = 1;  // written before the wait, so that only a failure writes after it
     uint32_t* m = s.lockw + (size_t)lock * s.stride;
     Wait w(ctl, (KIND == SP_MUTEX_SLEEP || KIND == SP_MUTEX_RING || KIND == SP_MUTEX_ARRAY ||
                  KIND == SP_MUTEX_COHORT || KIND == SP_MUTEX_CU_COHORT ||
@@ -215,19 +239,19 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
     Backoff bo(s.bo);
     bool ok = true;
     if constexpr (KIND == SP_MUTEX_SPIN_CAS || KIND == SP_MUTEX_SPIN_BACKOFF) {
-      while (cas_relaxed(m, 0, 1) != 0) {
+      while (uniform(cas_relaxed(m, 0, 1)) != 0) {
         bo(s.bo);
         if (!(ok = w.tick())) break;
       }
     } else if constexpr (KIND == SP_MUTEX_SPIN_EXCH) {
-      while (exch_relaxed(m, 1) != 0) {
+      while (uniform(exch_relaxed(m, 1)) != 0) {
         bo(s.bo);
         if (!(ok = w.tick())) break;
       }
     } else if constexpr (KIND == SP_MUTEX_TICKET) {
       const uint32_t my = add_relaxed(s.ticket + (size_t)lock * s.stride, 1);
       const uint32_t* turn = s.turn + (size_t)lock * s.stride;
-      while (ld_relaxed(turn) != my) {
+      while (uniform(ld_relaxed(turn)) != uniform(my)) {
         bo(s.bo);
         if (!(ok = w.tick())) break;
       }
@@ -289,37 +313,37 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
       }
     } else if constexpr (KIND == SP_MUTEX_CU_COHORT) {
       const uint32_t x = xcc_id(), c = cu_in_xcc();
-      const uint32_t tc = add_relaxed(cu_line(s, lock, x, c, 0), 1);
-      const uint32_t* cgrant = cu_line(s, lock, x, c, 1);
-      uint32_t* rec = cu_line(s, lock, x, c, 2);
-      st_cu(rec + 3, tc + 1);  // tell the holder that a later CU ticket was drawn
-      uint32_t v;
+      const uint32_t tc = uniform(add_relaxed(cu_line(s, lock, x, c, 0), 1));
+      uint32_t* line = cu_line(s, lock, x, c, 1);
+      st_cu(line + 1, tc + 1);  // tell the holder that a later CU ticket was drawn
+      u32x4 v;
       for (;;) {
-        v = ld_cu(cgrant);
-        if ((v & kTurnMask) == (tc & kTurnMask)) break;
+        v = ld_cu128(line);
+        if (((uniform(v.x) ^ tc) & kTurnMask) == 0) break;
         if (!(ok = w.tick())) break;
       }
-      const uint32_t kc = v >> 24;
+      const uint32_t kc = uniform(v.x) >> 24;
       uint32_t t = 0, k = 0, g = 0;
       if (ok && kc > 0) {
-        // This CU's cohort holds the XCD lock: its record says how, and the previous
+        // This CU's cohort holds the XCD lock: the record says how, and the previous
         // holder ran on this CU, whose L1 its stores went through (no acquire).
-        t = ld_cu(rec);
-        k = ld_cu(rec + 1);
-        g = ld_cu(rec + 2);
+        t = v.z & kTurnMask;
+        k = v.z >> 24;
+        g = v.w;
       } else if (ok) {
         ok = detail::cohort_acquire(s, lock, x, w, &t, &k, &g);
         if constexpr (FENCED) fence_acquire();
-        // for the CU's later holders of this session (complete before the first CU grant)
-        st_cu(rec, t);
-        st_cu(rec + 1, k);
-        st_cu(rec + 2, g);
+        // for the CU's later holders of this session (before the first CU grant)
+        st_xcd64(reinterpret_cast<uint64_t*>(line + 2),
+                 ((uint64_t)g << 32) | (k << 24) | (t & kTurnMask));
       }
       hold->ticket = t;
       hold->session = k;
       hold->global = g;
       hold->cu_ticket = tc;
       hold->cu_session = kc;
+      hold->cu_pass = kc + 1 < s.cohort_bound && (int32_t)(uniform(v.y) - (tc + 1)) > 0;
+      hold->cu = line;
     } else if constexpr (KIND == SP_MUTEX_MCS) {
       uint32_t* node = mcs_node(s, lock, blockIdx.x);
       st_relaxed(node, 0);      // next: none
@@ -328,25 +352,25 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
       const uint32_t prev = exch_relaxed(m, blockIdx.x + 1);
       if (prev != 0) {
         st_relaxed(mcs_node(s, lock, prev - 1), blockIdx.x + 1);  // predecessor.next = me
-        while (ld_relaxed(node + 1) != 0)
+        while (uniform(ld_relaxed(node + 1)) != 0)
           if (!(ok = w.tick())) break;
       }
     } else if constexpr (KIND == SP_MUTEX_ARRAY) {
       const uint32_t t = add_relaxed(s.ticket + (size_t)lock * s.stride, 1);
       const uint32_t* slot =
           s.queue + ((size_t)lock * s.qlen + (t & (s.qlen - 1))) * s.qstride;
-      while (ld_relaxed(slot) != t)
+      while (uniform(ld_relaxed(slot)) != uniform(t))
         if (!(ok = w.tick())) break;
       if (hold) hold->ticket = t;
     } else {
       for (;;) {
-        while (ld_relaxed(m) != 0)
+        while (uniform(ld_relaxed(m)) != 0)
           if (!(ok = w.tick())) break;
         if (!ok || cas_relaxed(m, 0, 1) == 0) break;
       }
     }
     if constexpr (FENCED && KIND != SP_MUTEX_CU_COHORT) fence_acquire();
-    s_ok = ok;
+    if (!ok) s_ok = 0;
   }
   __syncthreads();
   return s_ok;
@@ -390,27 +414,51 @@ __device__ void mutex_unlock(const MutexState& s, uint32_t lock, const MutexHold
     return;
   }
   if constexpr (KIND == SP_MUTEX_CU_COHORT) {
-    // Whether a later CU ticket was drawn comes from the waiters' announcement in the
-    // CU's L1, not from the ticket counter at memory: no round trip on a CU hand-over (a
-    // stale announcement only ends the CU's session early).
-    const uint32_t x = xcc_id(), c = cu_in_xcc();
-    const uint32_t drawn_c = is_leader() ? ld_cu(cu_line(s, lock, x, c, 2) + 3) : 0;
+    // A hand-over within the CU waits for nothing: once every wavefront has issued its
+    // stores (the workgroup barrier), the grant goes into the L1 behind them, and the next
+    // holder's loads go in behind its view of the grant -- what orders the wavefronts of
+    // one workgroup orders those of one CU.  Whether the stores have reached the L2
+    // matters to the next CU only, so each holder counts itself complete afterwards, in
+    // ticket order, and the one that hands the XCD lock on first waits for the holders
+    // before it.  Whether a later CU ticket was drawn comes from the waiters' announcement,
+    // as of this holder's entry or, if it showed none then, as of now (a stale one only
+    // ends the CU's session early).  Agent-scope critical sections (not FENCED) complete
+    // before any grant, since their data is not in this L1.
+    __syncthreads();
+    const uint32_t tc = hold->cu_ticket, kc = hold->cu_session + 1;
+    uint32_t* line = hold->cu;
+    const uint32_t grant = (kc << 24) | ((tc + 1) & kTurnMask);
+    bool pass = false;
+    uint32_t drawn = 0;
+    if (is_leader()) {
+      if (FENCED && hold->cu_pass) {  // no load, so no wait, between here and the store
+        st_cu(line, grant);
+        pass = true;
+      } else {
+        if (kc < s.cohort_bound) pass = (int32_t)(uniform(ld_cu(line + 1)) - (tc + 1)) > 0;
+        if (FENCED && pass) st_cu(line, grant);
+        if (!pass) drawn = ld_relaxed(cohort_ticket(s, lock, xcc_id()));
+      }
+    }
     wave_stores_complete();
     __syncthreads();
     if (!is_leader()) return;
-    uint32_t* cgrant = cu_line(s, lock, x, c, 1);
-    const uint32_t tc = hold->cu_ticket, kc = hold->cu_session + 1;
-    const uint32_t next_turn = (tc + 1) & kTurnMask;
-    if ((int32_t)(drawn_c - (tc + 1)) > 0 && kc < s.cohort_bound) {
-      // The next holder runs on this CU: it keeps the XCD lock and reads the critical
-      // section's stores through this CU's L1 (they have completed): no cache maintenance.
-      st_cu(cgrant, (kc << 24) | next_turn);
-    } else {
-      const uint32_t drawn = ld_relaxed(cohort_ticket(s, lock, x));
-      detail::cohort_release<FENCED>(s, lock, x, drawn, hold->ticket, hold->session + 1,
+    if constexpr (FENCED) {
+      uint32_t* done = line + s.qstride;
+      Wait w(ctl ? *ctl : Ctl{nullptr, 0}, 0);
+      while (uniform(ld_cu(done)) != uniform(tc))
+        if (ctl && !w.tick()) return;
+      if (!pass)
+        detail::cohort_release<FENCED>(s, lock, xcc_id(), drawn, hold->ticket,
+                                       hold->session + 1, hold->global);
+      st_cu(done, tc + 1);
+      if (pass) return;
+    } else if (!pass) {
+      detail::cohort_release<FENCED>(s, lock, xcc_id(), drawn, hold->ticket, hold->session + 1,
                                      hold->global);
-      st_cu(cgrant, next_turn);  // session 0: the CU's next holder takes the XCD lock
     }
+    // session 0 when the XCD lock went on: the CU's next holder takes it anew
+    st_cu(line, pass ? grant : grant & kTurnMask);
     return;
   }
   wave_stores_complete();

@@ -45,6 +45,7 @@ __global__ SP_FULL_OCCUPANCY void k_mutex(sp::MutexState s, uint32_t nlocks, uin
   const sp::Ctl ctl{err, sp::wall_clock() + timeout};
   const uint32_t b = blockIdx.x;
   const uint64_t A = total / nwg + (b < total % nwg ? 1 : 0);
+  const uint32_t lanes = sp::computed_here(blockDim.x);  // a load from the dispatch packet
   sp::MutexHold hold{0, 0};  // persists: the adaptive mutex learns across acquisitions
   for (uint64_t j = 0; j < A; ++j) {
     const uint32_t lock = sp::sched_key(seed, b, (uint32_t)j, 1) % nlocks;
@@ -55,9 +56,9 @@ __global__ SP_FULL_OCCUPANCY void k_mutex(sp::MutexState s, uint32_t nlocks, uin
       sp::cas_relaxed(err, sp::DEV_OK, sp::DEV_PARITY);
     uint32_t* wp = words + (size_t)lock * wstride;
     if constexpr (FENCED) {
-      for (uint32_t w = threadIdx.x; w < W; w += blockDim.x) wp[w] = wp[w] + 1;
+      for (uint32_t w = threadIdx.x; w < W; w += lanes) wp[w] = wp[w] + 1;
     } else {  // coherent critical section: agent-scope loads and stores
-      for (uint32_t w = threadIdx.x; w < W; w += blockDim.x)
+      for (uint32_t w = threadIdx.x; w < W; w += lanes)
         sp::st_relaxed(wp + w, sp::ld_relaxed(wp + w) + 1);
     }
     if (own && sp::is_leader() && sp::exch_relaxed(own, 0) != b + 1)

@@ -31,3 +31,39 @@ def test_xcd_chain_slots(ctx, K, nwg, lanes, total, coherent):
     assert 1 <= r["maxocc"] <= K and r["occ"] == 0
     assert r["state"][1:] == (total, total, total)
     assert int(r["data"].astype("u8").sum()) == total
+
+
+@pytest.mark.parametrize("passes", [1, 2, 255])
+@pytest.mark.parametrize("nwg,lanes,L,W", [
+    (2048, 64, 1, 1),      # one wavefront, one word
+    (2048, 256, 3, 257),   # stores of four wavefronts over nine lines
+    (512, 1024, 2, 1000),  # sixteen wavefronts, two workgroups per CU
+    (777, 192, 1, 33),     # CUs with three and with four contenders
+])
+def test_cu_cohort_handover(ctx, nwg, lanes, L, W, passes):
+    """A hand-over within a CU waits for no store; the one that leaves the CU waits for
+    every holder before it.  Each word's count is exact however often the lock moves."""
+    import paper_1110_4623_amd as sp
+    announce("cu cohort", nwg, lanes, L, W, passes)
+    m = sp.Mutex(ctx, "cu_cohort", L, W, cohort_passes=passes, verify=1)
+    try:
+        words, st, _ = m.run(nwg, lanes, 12_345, 50, 3)
+    finally:
+        m.close()
+    assert st["device_error"] == 0
+    assert (words == oracle.mutex_closed(3, nwg, 12_345, L, W)).all()
+
+
+@pytest.mark.parametrize("passes", [1, 3, 255])
+@pytest.mark.parametrize("pad", [4, 128])
+def test_xcd_cohort_handover(ctx, pad, passes):
+    """Grants through the XCD's L2, also where words of several XCDs share a line."""
+    import paper_1110_4623_amd as sp
+    announce("cohort", pad, passes)
+    m = sp.Mutex(ctx, "cohort", 5, 70, cohort_passes=passes, pad_bytes=pad, verify=1)
+    try:
+        words, st, _ = m.run(600, 128, 20_001, 100, 3)
+    finally:
+        m.close()
+    assert st["device_error"] == 0
+    assert (words == oracle.mutex_closed(3, 600, 20_001, 5, 70)).all()
