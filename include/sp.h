@@ -267,8 +267,10 @@ void sp_params_default(sp_params* p);
  * Section 7: tuning backoff per GPU and contention level).  Until a call replaces them,
  * the defaults are a tuning pass's winners on an MI355X: barrier central (low) and
  * per-XCD with 64 stamp copies (high); mutex spin with the paper's backoff, I_max 8
- * (low) and the CU-cohort lock (high; a run with fewer than two workgroups per CU and
- * lock runs the XCD-cohort lock with the same parameters instead); semaphore the per-XCD
+ * (low; a run with at least six workgroups per lock -- 16 for coherent_cs -- and three per
+ * XCD runs the XCD-cohort lock instead, while the bucket holds the built-in default) and
+ * the CU-cohort lock (high; a run with fewer than 2.5 workgroups per CU and lock -- five
+ * for coherent_cs -- runs the XCD-cohort lock with the same parameters instead); semaphore the per-XCD
  * chains (both; outside their range of K the chain kind, then the array kind; K = 1 with
  * at least two workgroups per CU SP_SEM_CU_LOCK).                                       */
 int sp_set_default(sp_ctx* ctx, uint32_t primitive, uint32_t bucket, uint32_t kind,

@@ -215,6 +215,7 @@ int sp_init(int device, sp_ctx** out) {
     for (int b = 0; b < 2; ++b) {
       sp_params_default(&ctx->defaults[prim][b].p);
       ctx->defaults[prim][b].kind = 0;
+      ctx->defaults[prim][b].builtin = true;
     }
   ctx->defaults[0][0].kind = SP_BARRIER_CENTRAL;  // 1.7 us/round at 16 workgroups
   ctx->defaults[0][0].p.poll_sleep = 0;
@@ -291,6 +292,7 @@ int sp_set_default(sp_ctx* ctx, uint32_t primitive, uint32_t bucket, uint32_t ki
   SP_CHECK(spi::normalize(ctx, p, &q));
   ctx->defaults[primitive][bucket].kind = kind;
   ctx->defaults[primitive][bucket].p = q;
+  ctx->defaults[primitive][bucket].builtin = false;
   return SP_OK;
 }
 

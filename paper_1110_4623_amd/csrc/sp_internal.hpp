@@ -12,6 +12,7 @@
 struct sp_default_entry {
   uint32_t kind;
   sp_params p;
+  bool builtin;  // the library's own entry: its kind may give way to another by size
 };
 
 struct sp_ctx {
@@ -138,13 +139,28 @@ inline uint32_t bucket_of(uint32_t contenders) { return contenders >= 64 ? 1u : 
 // to 32 workgroups and the per-XCD barrier from 48 on (1.75 / 2.39 / 3.88 against 2.72 /
 // 2.72 / 2.85 us per round at 16 / 32 / 48, 256 lanes), so the high bucket starts at 40.
 inline uint32_t barrier_bucket_of(uint32_t nwg) { return nwg >= 40 ? 1u : 0u; }
-// A default mutex whose bucket names the CU-cohort lock runs it only where a lock has at
-// least two contenders per CU on average; below that few hand-overs stay within a CU and
-// the XCD-cohort lock is faster (one lock, 16 words, M acquisitions/s, XCD-cohort
-// against CU-cohort: 256 workgroups 0.78 / 0.71, 512 0.78 / 0.93, 1024 0.77 / 1.18, 2048
-// 0.74 / 1.13; 2048 workgroups on 8 locks 6.58 / 6.91, on 16 locks 13.1 / 12.7).
-inline bool cu_cohort_pays(uint64_t nwg, uint64_t nlocks, uint64_t cu_count) {
-  return nwg >= 2 * nlocks * cu_count;
+// A default mutex whose bucket names the CU-cohort lock runs it only where a lock has
+// enough contenders per CU; below that few hand-overs stay within a CU and the XCD-cohort
+// lock is faster.  M acquisitions/s, CU-cohort / XCD-cohort, 16 words: plain data, one lock,
+// 512 workgroups 0.93 / 1.02, 640 1.15 / 1.02, 1024 1.59 / 1.02; 2048 workgroups on 2
+// locks 2.52 / 2.10, 3 3.41 / 3.21, 4 4.26 / 4.25, 6 5.88 / 6.36: from 2.5 per CU and lock.
+// Coherent data, whose sections go to memory whatever the hand-over: one lock, 1024
+// workgroups 1.11 / 1.03; 2048 on 2 locks 2.08 / 2.09, on 3 3.02 / 3.16: from 5.
+inline bool cu_cohort_pays(uint64_t nwg, uint64_t nlocks, uint64_t cu_count, bool coherent) {
+  return 2 * nwg >= (coherent ? 10 : 5) * nlocks * cu_count;
+}
+// The K = 1 semaphore's line between one chain and the CU-cohort lock.
+inline bool cu_lock_pays(uint64_t nwg, uint64_t cu_count) { return nwg >= 2 * cu_count; }
+// A default mutex whose low bucket is the library's own (the spin lock with the paper's
+// backoff) runs the XCD-cohort lock where a lock has enough contenders that some of them
+// share an XCD.  M acquisitions/s, spin / XCD-cohort, 16 words: plain data, 64 workgroups
+// on 16 locks 9.4 / 9.0, 96 10.1 / 10.3, 128 10.2 / 11.2, 256 10.6 / 13.2; 600 on 100 39.5
+// / 43.0; 2048 on 256 53.9 / 62.9, on 64 28 / 48; 8 on one
+// lock 0.80 / 0.62 (one per XCD), 24 on 3 2.24 / 2.27: from six per lock and three per XCD.
+// Coherent data, where there is no writeback to save: 128 on 16 locks 14.0 / 13.5, 256 14.5
+// / 14.4, 2048 on 128 102 / 106, on 64 38 / 59: from 16 per lock.
+inline bool cohort_pays(uint64_t nwg, uint64_t nlocks, uint64_t xcds, bool coherent) {
+  return nwg >= (coherent ? 16 : 6) * nlocks && nwg >= 3 * xcds;
 }
 
 }  // namespace spi

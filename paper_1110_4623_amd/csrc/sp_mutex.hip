@@ -137,8 +137,10 @@ int sp_mutex_create(sp_ctx* ctx, uint32_t kind, uint32_t nlocks, uint32_t words_
     // the CU-cohort lock runs only with two contenders per CU and lock, which a grid of
     // at most maxThreadsPerMultiProcessor / 64 workgroups per CU may not reach
     const uint64_t max_wg = (uint64_t)ctx->cu_count * (ctx->prop.maxThreadsPerMultiProcessor / 64);
-    if (dk == SP_MUTEX_CU_COHORT && !spi::cu_cohort_pays(max_wg, nlocks, ctx->cu_count))
+    if (dk == SP_MUTEX_CU_COHORT &&
+        !spi::cu_cohort_pays(max_wg, nlocks, ctx->cu_count, q.coherent_cs != 0))
       dk = SP_MUTEX_COHORT;
+    if (b == 0 && d.builtin) dk = SP_MUTEX_COHORT;  // what its spin lock gives way to
     if (dk == SP_MUTEX_COHORT || dk == SP_MUTEX_CU_COHORT)
       words = std::max(words, cohort_words(dk, nlocks, spi::stride_words(d.p)));
   }
@@ -190,8 +192,17 @@ int sp_mutex_run(sp_mutex* m, uint32_t nwg, uint32_t lanes, uint64_t total_acq,
     q = d.p;
     q.timeout_ms = t;
     q.coherent_cs = m->p.coherent_cs;  // a property of the caller's critical sections
-    if (kind == SP_MUTEX_CU_COHORT && !spi::cu_cohort_pays(nwg, m->nlocks, ctx->cu_count))
+    const bool coherent = q.coherent_cs != 0;
+    if (kind == SP_MUTEX_CU_COHORT &&
+        !spi::cu_cohort_pays(nwg, m->nlocks, ctx->cu_count, coherent))
       kind = SP_MUTEX_COHORT;
+    // (a lock count whose cohort state was not allocated at creation stays with the spin lock)
+    if (kind == SP_MUTEX_SPIN_BACKOFF && d.builtin &&
+        spi::cohort_pays(nwg, m->nlocks, ctx->xcd_count, coherent) &&
+        cohort_words(SP_MUTEX_COHORT, m->nlocks, spi::stride_words(q)) <= m->queue_words) {
+      kind = SP_MUTEX_COHORT;
+      q.poll_sleep = 0;
+    }
   }
   if (kind == SP_MUTEX_SPIN_BACKOFF && q.backoff == SP_BACKOFF_NONE) q.backoff = SP_BACKOFF_EXP;
   if (kind == SP_MUTEX_SPIN_CAS || kind == SP_MUTEX_SLEEP || kind == SP_MUTEX_ADAPTIVE ||

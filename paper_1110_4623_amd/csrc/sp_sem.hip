@@ -272,7 +272,7 @@ int sp_sem_run(sp_sem* sem, uint32_t nwg, uint32_t lanes, uint64_t total_pairs,
     if (kind == SP_SEM_CHAIN && sem->K > kCohortSlots) kind = SP_SEM_ARRAY;
     // K = 1 with at least two workgroups per CU: the CU-cohort lock (2048 workgroups,
     // holds U[0, 2000] clocks: 0.76 against 0.59 M pairs/s for one chain, fenced)
-    if (kind == SP_SEM_CHAIN && sem->K == 1 && spi::cu_cohort_pays(nwg, 1, ctx->cu_count))
+    if (kind == SP_SEM_CHAIN && sem->K == 1 && spi::cu_lock_pays(nwg, ctx->cu_count))
       kind = SP_SEM_CU_LOCK;
   }
   if (kind == SP_SEM_SPIN_BACKOFF && q.backoff == SP_BACKOFF_NONE) {

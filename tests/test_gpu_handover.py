@@ -67,3 +67,29 @@ def test_xcd_cohort_handover(ctx, pad, passes):
         m.close()
     assert st["device_error"] == 0
     assert (words == oracle.mutex_closed(3, 600, 20_001, 5, 70)).all()
+
+
+@pytest.mark.parametrize("coherent", [0, 1])
+@pytest.mark.parametrize("nwg,L", [
+    (24, 4), (23, 3), (25, 5), (96, 6), (95, 6),   # around the spin / XCD-cohort lines
+    (639, 1), (640, 1), (1280, 1), (1279, 1),      # around the XCD-cohort / CU-cohort lines
+])
+def test_default_mutex_lines(ctx, nwg, L, coherent):
+    """A default mutex on both sides of each line, the first run of every mutex recorded
+    into a graph (so nothing is allocated for it) and replayed with runs in between."""
+    import paper_1110_4623_amd as sp
+    announce("default mutex", nwg, L, coherent)
+    want = oracle.mutex_closed(9, nwg, 3000, L, 9)
+    m = sp.Mutex(ctx, "default", L, 9, coherent_cs=coherent)
+    g = sp.Graph(ctx)
+    try:
+        with g:
+            m.launch(nwg, 64, 3000, 100, 9)
+        for _ in range(2):
+            g.launch(2)
+            assert (m.words() == want).all()
+            words, _, _ = m.run(nwg, 64, 3000, 100, 9)
+            assert (words == want).all()
+    finally:
+        g.close()
+        m.close()
