@@ -225,15 +225,36 @@ struct Wait {
   // and the deadline.  Returns false when the wait must be abandoned.
   __device__ __forceinline__ bool tick() {
     sleep_units(poll_sleep);
-    if ((++n & 63) != 0) return true;
-    if (uniform(ld_relaxed(ctl.err)) != DEV_OK) return false;
-    if (wall_clock() > ctl.deadline) {
-      cas_relaxed(ctl.err, DEV_OK, DEV_TIMEOUT);
-      return false;
+    uint32_t go = 1;
+    if ((++n & 63) == 0) {
+      go = uniform(ld_relaxed(ctl.err)) == DEV_OK;
+      if (wall_clock() > ctl.deadline) {
+        cas_relaxed(ctl.err, DEV_OK, DEV_TIMEOUT);
+        go = 0;
+      }
     }
-    return true;
+    return uniform(go) != 0;  // (the compiler does not split the loop at its outcomes)
   }
 };
+
+// Polls until seen() holds (true) or the watchdog ends the wait (false).  One exit, whose
+// outcome the compiler cannot follow: a loop left by two ways compiles to a chain of flags
+// and branches that the successful poll runs through too (~40 clocks).
+template <class Seen>
+__device__ __forceinline__ bool poll(Wait& w, Seen seen) {
+  uint32_t got;
+  do got = seen();
+  while (!got && w.tick());
+  return uniform(got) != 0;
+}
+// The same by several lanes, each waiting for its own word.
+template <class Seen>
+__device__ __forceinline__ bool poll_each(Wait& w, Seen seen) {
+  bool got;
+  do got = seen();
+  while (!got && w.tick());
+  return got;
+}
 
 // ---- backoff (Section 5, Mutex) -----------------------------------------------------
 struct BackoffCfg {

@@ -67,15 +67,16 @@ constexpr uint32_t kArriveWords = 4;
 
 namespace detail {
 
+// By the leader alone.
 __device__ __forceinline__ bool poll_until(const uint32_t* p, uint32_t stamp, Wait& w) {
-  while (!reached(ld_relaxed(p), stamp))
-    if (!w.tick()) return false;
-  return true;
+  return poll(w, [&] { return reached(uniform(ld_relaxed(p)), stamp); });
 }
 __device__ __forceinline__ bool poll_until_cu(const uint32_t* p, uint32_t stamp, Wait& w) {
-  while (!reached(ld_cu(p), stamp))
-    if (!w.tick()) return false;
-  return true;
+  return poll(w, [&] { return reached(uniform(ld_cu(p)), stamp); });
+}
+// By several lanes, each its own word.
+__device__ __forceinline__ bool poll_until_each(const uint32_t* p, uint32_t stamp, Wait& w) {
+  return poll_each(w, [&] { return reached(ld_relaxed(p), stamp); });
 }
 
 // Leader part of the counter-based barriers.  Each leader publishes its workgroup's
@@ -304,7 +305,7 @@ __device__ __forceinline__ bool xcd_wait(uint32_t stamp, const Ctl& ctl, const X
     // Coherent data: no cache maintenance, so nothing is shared per CU; every workgroup
     // polls the populated XCDs' stamps itself (two flag hops per round).
     if (threadIdx.x < X && ((xmask >> threadIdx.x) & 1))
-      ok = poll_until(stamps + (size_t)threadIdx.x * sstride, stamp, w);
+      ok = poll_until_each(stamps + (size_t)threadIdx.x * sstride, stamp, w);
     return and_sync(ok, stamp, fail);
   }
   // this CU's release line
@@ -315,7 +316,7 @@ __device__ __forceinline__ bool xcd_wait(uint32_t stamp, const Ctl& ctl, const X
     // a kernel on another stream reads on this XCD before then (say, other words of a
     // line that participants elsewhere write) would otherwise stay stale in the L2.
     if (threadIdx.x < X && ((xmask >> threadIdx.x) & 1))
-      ok = poll_until(stamps + (size_t)threadIdx.x * sstride, stamp, w);
+      ok = poll_until_each(stamps + (size_t)threadIdx.x * sstride, stamp, w);
     ok = and_sync(ok, stamp, fail);
     if (!ok) return false;
     if (is_leader()) {

@@ -36,10 +36,8 @@ __device__ bool cond_wait(const CondState& cv, const MutexState& m, uint32_t loc
   mutex_unlock<MKIND, FENCED>(m, lock, hold);
   if (is_leader()) {
     Wait w(ctl, cv.poll_sleep);
-    bool ok = true;
-    while (!((int32_t)(ld_relaxed(cv.signals) - s_ticket) > 0))
-      if (!(ok = w.tick())) break;
-    s_ok = ok;
+    const uint32_t t = s_ticket;
+    s_ok = poll(w, [&] { return (int32_t)uniform(ld_relaxed(cv.signals) - t) > 0; });
   }
   __syncthreads();
   if (!s_ok) return false;

@@ -97,22 +97,21 @@ __device__ __forceinline__ bool drawn_after(uint32_t drawn, uint32_t t) {
 __device__ __forceinline__ bool cohort_acquire(const MutexState& s, uint32_t lock, uint32_t x,
                                                Wait& w, uint32_t* t, uint32_t* k,
                                                uint32_t* g) {
-  bool ok = true;
-  *t = add_relaxed(cohort_ticket(s, lock, x), 1);
-  const uint64_t* grant = uniform_ptr(cohort_grant(s, lock, x, *t));
+  const uint32_t my = uniform(add_relaxed(cohort_ticket(s, lock, x), 1));
+  const uint64_t* grant = uniform_ptr(cohort_grant(s, lock, x, my));
   uint64_t v;
-  for (;;) {
+  bool ok = poll(w, [&] {
     v = ld_xcd64(grant);  // written on this XCD
-    if (((uint32_t)v & kTurnMask) == (uniform(*t) & kTurnMask)) break;
-    if (!(ok = w.tick())) break;
-  }
+    return (((uint32_t)v ^ my) & kTurnMask) == 0;
+  });
+  *t = my;
   *k = ((uint32_t)v >> 24) & 0xFF;
   *g = (uint32_t)(v >> 32);
   if (ok && *k == 0) {  // the cohort does not hold the global lock: queue for it
-    *g = add_relaxed(s.ticket + (size_t)lock * s.stride, 1);
+    const uint32_t all = uniform(add_relaxed(s.ticket + (size_t)lock * s.stride, 1));
     const uint32_t* turn = s.turn + (size_t)lock * s.stride;
-    while (uniform(ld_relaxed(turn)) != uniform(*g))
-      if (!(ok = w.tick())) break;
+    ok = poll(w, [&] { return uniform(ld_relaxed(turn)) == all; });
+    *g = all;
   }
   return ok;
 }
@@ -239,22 +238,25 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
     Backoff bo(s.bo);
     bool ok = true;
     if constexpr (KIND == SP_MUTEX_SPIN_CAS || KIND == SP_MUTEX_SPIN_BACKOFF) {
-      while (uniform(cas_relaxed(m, 0, 1)) != 0) {
-        bo(s.bo);
-        if (!(ok = w.tick())) break;
-      }
+      ok = poll(w, [&] {
+        const bool got = uniform(cas_relaxed(m, 0, 1)) == 0;
+        if (!got) bo(s.bo);
+        return got;
+      });
     } else if constexpr (KIND == SP_MUTEX_SPIN_EXCH) {
-      while (uniform(exch_relaxed(m, 1)) != 0) {
-        bo(s.bo);
-        if (!(ok = w.tick())) break;
-      }
+      ok = poll(w, [&] {
+        const bool got = uniform(exch_relaxed(m, 1)) == 0;
+        if (!got) bo(s.bo);
+        return got;
+      });
     } else if constexpr (KIND == SP_MUTEX_TICKET) {
-      const uint32_t my = add_relaxed(s.ticket + (size_t)lock * s.stride, 1);
+      const uint32_t my = uniform(add_relaxed(s.ticket + (size_t)lock * s.stride, 1));
       const uint32_t* turn = s.turn + (size_t)lock * s.stride;
-      while (uniform(ld_relaxed(turn)) != uniform(my)) {
-        bo(s.bo);
-        if (!(ok = w.tick())) break;
-      }
+      ok = poll(w, [&] {
+        const bool got = uniform(ld_relaxed(turn)) == my;
+        if (!got) bo(s.bo);
+        return got;
+      });
       if (hold) hold->ticket = my;
     } else if constexpr (KIND == SP_MUTEX_ADAPTIVE) {
       const uint32_t my = add_relaxed(s.ticket + (size_t)lock * s.stride, 1);
@@ -297,11 +299,10 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
       const uint32_t mask = s.qlen - 1;
       st_relaxed(q + (size_t)(t & mask) * s.qstride, t + 1);
       const uint32_t* head = s.turn + (size_t)lock * s.stride;
-      for (;;) {
+      ok = poll(w, [&] {
         const uint32_t h = ld_relaxed(head);
-        if (ld_relaxed(q + (size_t)(h & mask) * s.qstride) == t + 1) break;
-        if (!(ok = w.tick())) break;
-      }
+        return uniform(ld_relaxed(q + (size_t)(h & mask) * s.qstride)) == uniform(t + 1);
+      });
       if (hold) hold->ticket = t;
     } else if constexpr (KIND == SP_MUTEX_COHORT) {
       uint32_t t, k, g;
@@ -317,11 +318,10 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
       uint32_t* line = cu_line(s, lock, x, c, 1);
       st_cu(line + 1, tc + 1);  // tell the holder that a later CU ticket was drawn
       u32x4 v;
-      for (;;) {
+      ok = poll(w, [&] {
         v = ld_cu128(line);
-        if (((uniform(v.x) ^ tc) & kTurnMask) == 0) break;
-        if (!(ok = w.tick())) break;
-      }
+        return ((uniform(v.x) ^ tc) & kTurnMask) == 0;
+      });
       const uint32_t kc = uniform(v.x) >> 24;
       uint32_t t = 0, k = 0, g = 0;
       if (ok && kc > 0) {
@@ -352,22 +352,17 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
       const uint32_t prev = exch_relaxed(m, blockIdx.x + 1);
       if (prev != 0) {
         st_relaxed(mcs_node(s, lock, prev - 1), blockIdx.x + 1);  // predecessor.next = me
-        while (uniform(ld_relaxed(node + 1)) != 0)
-          if (!(ok = w.tick())) break;
+        ok = poll(w, [&] { return uniform(ld_relaxed(node + 1)) == 0; });
       }
     } else if constexpr (KIND == SP_MUTEX_ARRAY) {
       const uint32_t t = add_relaxed(s.ticket + (size_t)lock * s.stride, 1);
       const uint32_t* slot =
           s.queue + ((size_t)lock * s.qlen + (t & (s.qlen - 1))) * s.qstride;
-      while (uniform(ld_relaxed(slot)) != uniform(t))
-        if (!(ok = w.tick())) break;
+      ok = poll(w, [&] { return uniform(ld_relaxed(slot)) == uniform(t); });
       if (hold) hold->ticket = t;
     } else {
-      for (;;) {
-        while (uniform(ld_relaxed(m)) != 0)
-          if (!(ok = w.tick())) break;
-        if (!ok || cas_relaxed(m, 0, 1) == 0) break;
-      }
+      do ok = poll(w, [&] { return uniform(ld_relaxed(m)) == 0; });
+      while (ok && uniform(cas_relaxed(m, 0, 1)) != 0);
     }
     if constexpr (FENCED && KIND != SP_MUTEX_CU_COHORT) fence_acquire();
     if (!ok) s_ok = 0;

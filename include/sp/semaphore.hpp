@@ -255,6 +255,7 @@ __device__ bool sem_wait(const SemState& s, const Ctl& ctl, SemHold* hold = null
     return mutex_lock<SP_MUTEX_CU_COHORT, FENCED>(cu_lock_state(s), 0, ctl, &hold->lock);
   __shared__ uint32_t s_ok;
   if (is_leader()) {
+    s_ok = 1;  // written before the wait, so that only a failure writes after it
     bool ok = true;
     if constexpr (KIND == SP_SEM_SPIN || KIND == SP_SEM_SPIN_BACKOFF) {
       Wait w(ctl, 0);
@@ -314,11 +315,10 @@ __device__ bool sem_wait(const SemState& s, const Ctl& ctl, SemHold* hold = null
         const uint32_t t = add_relaxed(cq_drawn(s, x), 1);
         uint64_t* slot = cq_slot(s, x, t);
         uint64_t v = 0;
-        for (;;) {
+        ok = poll(w, [&] {
           v = ld_relaxed64(slot);
-          if ((uint32_t)v == t + 1) break;
-          if (!(ok = w.tick())) break;
-        }
+          return uniform((uint32_t)v) == uniform(t + 1);
+        });
         if (ok) {
           k = (uint32_t)(v >> 32);
           st_relaxed64(slot, 0);  // taken: the slot may carry the grant of ticket t + len
@@ -335,11 +335,10 @@ __device__ bool sem_wait(const SemState& s, const Ctl& ctl, SemHold* hold = null
       if (t >= kx) {
         if (s.cq_local) {  // poster and waiter share the XCD's L2
           g = uniform_ptr(g);
-          while (ld_xcd64(g) <= t)
-            if (!(ok = w.tick())) break;
+          const uint64_t my = uniform(t);
+          ok = poll(w, [&] { return ld_xcd64(g) > my; });
         } else {
-          while (ld_relaxed64(g) <= t)
-            if (!(ok = w.tick())) break;
+          ok = poll(w, [&] { return uniform(ld_relaxed64(g)) > uniform(t); });
         }
       }
     } else if constexpr (KIND == SP_SEM_CHAIN) {
@@ -348,36 +347,31 @@ __device__ bool sem_wait(const SemState& s, const Ctl& ctl, SemHold* hold = null
       hold->ticket = t;
       const uint64_t* g = chain_slots(s, 0, s.K, s.chain_len, t, &hold->next);
       if (t >= s.K) {
-        while (ld_relaxed64(g) <= t)
-          if (!(ok = w.tick())) break;
+        ok = poll(w, [&] { return uniform(ld_relaxed64(g)) > uniform(t); });
       }
     } else if constexpr (KIND == SP_SEM_ARRAY) {
       Wait w(ctl, s.poll_sleep);
       const uint64_t t = add_relaxed64(as_tickets(s), 1);
       if (t >= s.K) {
         const uint64_t* g = as_slot(s, t);
-        while (ld_relaxed64(g) <= t)
-          if (!(ok = w.tick())) break;
+        ok = poll(w, [&] { return uniform(ld_relaxed64(g)) > uniform(t); });
       }
     } else if constexpr (KIND == SP_SEM_COUNTERS) {
       Wait w(ctl, s.poll_sleep);
       const uint32_t t = add_relaxed(s.ticket, 1);
       uint32_t posts = ld_relaxed(s.turn);  // in flight with the ticket; a lower bound
-      while (!((int32_t)(posts + s.K - t) > 0)) {
-        if (!(ok = w.tick())) break;
-        posts = ld_relaxed(s.turn);
-      }
+      if (!((int32_t)(posts + s.K - t) > 0))
+        ok = poll(w, [&] { return (int32_t)uniform(ld_relaxed(s.turn) + s.K - t) > 0; });
     } else {
       Wait w(ctl, KIND == SP_SEM_SLEEP ? s.poll_sleep : 0);
       const uint32_t old = add_relaxed(s.count, 1);
       if (old >= s.K) {  // at capacity: queue
         const uint32_t idx = add_relaxed(s.ticket, 1);
-        while (!((int32_t)(ld_relaxed(s.turn) - idx) > 0))
-          if (!(ok = w.tick())) break;
+        ok = poll(w, [&] { return (int32_t)uniform(ld_relaxed(s.turn) - idx) > 0; });
       }
     }
     if constexpr (FENCED) fence_acquire();
-    s_ok = ok;
+    if (!ok) s_ok = 0;
   }
   __syncthreads();
   return s_ok;
@@ -514,13 +508,13 @@ template <bool FENCE>
 __device__ __forceinline__ bool wsem_wait_leader(const WSemState& s, uint32_t u, const Ctl& ctl) {
   // The first load of `released` does not depend on the fetch-and-add, so both are in
   // flight together; a value older than the ticket is a lower bound and only delays.
-  const uint32_t end = add_relaxed(s.issued, u) + u;
-  uint32_t rel = ld_relaxed(s.released);
+  const uint32_t drawn = add_relaxed(s.issued, u);
+  const uint32_t rel = ld_relaxed(s.released);
+  const uint32_t end = drawn + u;
   Wait w(ctl, s.poll_sleep);
-  while (!reached(rel + s.K, end)) {
-    if (!w.tick()) return false;
-    rel = ld_relaxed(s.released);
-  }
+  if (!reached(rel + s.K, end) &&
+      !poll(w, [&] { return reached(uniform(ld_relaxed(s.released)) + s.K, uniform(end)); }))
+    return false;
   if constexpr (FENCE) fence_acquire();
   return true;
 }
