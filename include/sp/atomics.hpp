@@ -28,21 +28,30 @@
 
 namespace sp {
 
+// Every word a primitive touches is in global memory: said so, a pointer that went through
+// LDS or scalar registers still compiles to global accesses (flat ones check for LDS first).
+template <class T>
+using global_ptr = __attribute__((address_space(1))) T*;
+template <class T>
+__device__ __forceinline__ global_ptr<T> as_global(T* p) {
+  return (global_ptr<T>)p;
+}
+
 // ---- agent-scope atomics ------------------------------------------------------------
 __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(as_global(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_relaxed(uint32_t* p, uint32_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Workgroup-scope load and store: they may hit the CU's L1, which every wavefront on the
 // CU shares, so a store by one workgroup reaches another on the same CU without a trip to
 // memory (another CU's store is not seen until the L1 line is invalidated).
 __device__ __forceinline__ uint32_t ld_cu(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return __hip_atomic_load(as_global(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ __forceinline__ void st_cu(uint32_t* p, uint32_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 // Four words of one 16-byte aligned block at workgroup scope, in one access.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -53,10 +62,10 @@ __device__ __forceinline__ u32x4 ld_cu128(const uint32_t* p) {
   return v;
 }
 __device__ __forceinline__ uint64_t ld_relaxed64(const uint64_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(as_global(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_relaxed64(uint64_t* p, uint64_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // XCD-local signal: a store through to the XCD's L2 (workgroup scope: the L1 is
 // write-through) and a load served by that L2.  The vector L1 has no instruction that
@@ -68,7 +77,19 @@ __device__ __forceinline__ void st_relaxed64(uint64_t* p, uint64_t v) {
 // the line lives, an agent-scope store and poll 970-1780 (2000 hand-overs, two idle
 // workgroups).  `p` must be the same for the whole wavefront (uniform_ptr).
 __device__ __forceinline__ void st_xcd64(uint64_t* p, uint64_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void st_xcd8(uint8_t* p, uint8_t v) {
+  __hip_atomic_store(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// 64 bytes at once (p a multiple of 4).
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ u32x16 ld_xcd512(const uint8_t* p) {
+  u32x16 v;
+  __asm__ __volatile__(
+      "s_dcache_inv\n\ts_waitcnt lgkmcnt(0)\n\ts_load_dwordx16 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)"
+      : "=&s"(v) : "s"(p) : "memory");
+  return v;
 }
 __device__ __forceinline__ uint64_t ld_xcd64(const uint64_t* p) {
   uint64_t v;
@@ -96,10 +117,8 @@ __device__ __forceinline__ T* uniform_ptr(T* p) {
 // and the wait would keep the caller from doing anything while the value is on its way:
 // a pointer in vector registers, of which the compiler knows nothing, is left alone.
 template <class T>
-using global_ptr = __attribute__((address_space(1))) T*;
-template <class T>
 __device__ __forceinline__ global_ptr<T> lane_ptr(T* p) {
-  global_ptr<T> g = (global_ptr<T>)p;
+  global_ptr<T> g = as_global(p);
   __asm__("" : "+v"(g));
   return g;
 }
@@ -107,14 +126,14 @@ __device__ __forceinline__ uint32_t add_relaxed(uint32_t* p, uint32_t v) {
   return __hip_atomic_fetch_add(lane_ptr(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint32_t exch_relaxed(uint32_t* p, uint32_t v) {
-  return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_exchange(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint32_t max_relaxed(uint32_t* p, uint32_t v) {
   return __hip_atomic_fetch_max(lane_ptr(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Compare-and-swap; returns the value seen (== expected on success).
 __device__ __forceinline__ uint32_t cas_relaxed(uint32_t* p, uint32_t expected, uint32_t desired) {
-  __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED,
+  __hip_atomic_compare_exchange_strong(as_global(p), &expected, desired, __ATOMIC_RELAXED,
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return expected;
 }

@@ -22,7 +22,7 @@ struct BarrierState {
   uint32_t tgroups;     // groups of the counter tree (tree, xcd round 0 and fallback), <= nwg
   uint32_t flag_stride; // flag barrier: uint32 words between flags (1 = packed)
   uint32_t poll_sleep;  // s_sleep units between polls
-  uint32_t xblock;      // xcd: uint32 words of each XCD's block of local arrival flags
+  uint32_t xblock;      // xcd: members that each XCD's block of arrival flags takes
   uint32_t fenced;      // 1: order plain memory (release / acquire fences); 0: the data
                         // exchanged across the barrier is accessed with agent-scope
                         // loads and stores, so the barrier does no cache maintenance
@@ -49,8 +49,7 @@ struct BarrierState {
   uint32_t* overflow;   // xcd: registrations that did not fit (nonzero = tree fallback)
   uint32_t* xarrive;    // xcd: per-XCD arrival stamps (groups lines)
   uint32_t* lrelease;   // xcd: per-CU release lines (kCuLines per XCD)
-  uint32_t* larrive;    // xcd: arrival flags kArriveWords apart, XCD-major blocks of
-                        // xblock flags
+  uint32_t* larrive;    // xcd: XCD-major blocks of one arrival byte per member
   uint32_t* cu_count;   // xcd: workgroups registered per CU key (groups * 256 words)
   uint32_t* xcount;     // xcd: members registered per XCD (groups words)
   uint32_t* xcu;        // xcd: CU leaders registered per XCD (groups words)
@@ -60,9 +59,7 @@ struct BarrierState {
 
 // CUs with members per XCD that the per-XCD barrier takes (gfx950 has 32 per XCD).
 constexpr uint32_t kCuLines = 64;
-// Words between two arrival flags of an XCD's block: 16 bytes, eight flags per 128-byte
-// line.  Packed flags put 32 concurrent writers on every line and one line per flag
-// makes the master's scan touch a line per member; eight per line measured fastest.
+// Words kept per arrival flag of an XCD's block (the flags themselves are bytes, packed).
 constexpr uint32_t kArriveWords = 4;
 
 namespace detail {
@@ -218,8 +215,11 @@ __device__ __forceinline__ bool flag_wait(const BarrierState& s, uint32_t stamp,
 // sends workgroup w to XCD w mod 8, but not always (after a cooperative launch, for
 // example, later dispatches have been measured to start one XCD further on).  Later rounds:
 //   1. Each member waits for its own stores to complete (they are then in the XCD's L2)
-//      and stores its arrival stamp into its XCD's block of arrival flags (16 bytes
-//      apart); the master's lanes scan the block.
+//      and stores the low byte of its arrival stamp into its XCD's block of arrival bytes,
+//      through that L2 (st_xcd8); the master's wavefronts scan the block there, 64 members
+//      per load.  With 4-byte agent-scope flags 16 bytes apart the arrivals went to memory
+//      and back: 2048 workgroups 5.40 us per round, now 5.27; 1000 workgroups of 192 lanes,
+//      coherent data, 3.31, now 3.06.
 //   2. The master writes back the XCD's dirty L2 lines once for all its members (agent
 //      release) and publishes the XCD's stamp.
 //   3. Each CU leader polls the stamps of every XCD that has members; once all are
@@ -238,7 +238,10 @@ __device__ __forceinline__ bool flag_wait(const BarrierState& s, uint32_t stamp,
 // lines), so it is shared by the workgroups of one CU: all of them are waiting when
 // their leader invalidates, so nothing stale can re-enter the L1 before they read.
 // If an XCD holds more members than its flag block or more than kCuLines CUs, every
-// workgroup falls back to the counter tree.  All other flags are agent-scope atomics.
+// workgroup falls back to the counter tree.  The stamps are agent-scope atomics.  Having
+// only the master poll them and release its XCD through the L2 was slower (2048 workgroups
+// 5.40 against 5.27 plain, 3.49 against 3.34 coherent): what the shorter polls save, the
+// extra hop costs.
 struct XcdLocal {
   uint32_t x;        // the XCD this workgroup runs on
   uint32_t k;        // member index within the XCD (0 = master)
@@ -262,45 +265,73 @@ struct XcdLocal {
 // The master's stores of its stamp: copy c at pub[c] + the XCD's index in xmail.
 constexpr uint32_t kMaxCopies = 256;
 
+// The master's own arrival byte and the bytes that fill the last group of 64 carry the next
+// stamp ahead of time, so that a scan compares whole groups.
+__device__ __forceinline__ void arrive_ahead(uint8_t* block, uint32_t members, uint32_t stamp) {
+  const uint32_t lane = threadIdx.x & 63, i = (members & ~63u) + lane;
+  if (lane == 0) st_xcd8(block, (uint8_t)stamp);
+  if ((members & 63) && i >= members) st_xcd8(block + i, (uint8_t)stamp);
+}
+
+// Waits until every member's arrival byte equals the stamp's low byte (a member's byte is
+// one round behind or current, never further apart).  A wavefront takes 64 members per
+// load; the compare is scalar.
+__device__ __forceinline__ int scan_arrivals(const uint8_t* block, uint32_t members,
+                                             uint32_t stamp, Wait& w, uint32_t lanes) {
+  const uint64_t want = (stamp & 0xFF) * 0x0101010101010101ull;
+  const uint32_t wave = uniform(threadIdx.x >> 6);
+  for (uint32_t g = wave * 64; g < members; g += lanes) {
+    const uint8_t* p = uniform_ptr(block + g);
+    const bool ok = poll(w, [&] {
+      const u32x16 v = ld_xcd512(p);
+      uint64_t off = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) off |= (((uint64_t)v[2 * i + 1] << 32) | v[2 * i]) ^ want;
+      return off == 0;
+    });
+    if (!ok) return 0;
+  }
+  return 1;
+}
+
 __device__ __forceinline__ bool xcd_wait(uint32_t stamp, const Ctl& ctl, const XcdLocal& L,
                                          const uint32_t* pub, uint32_t* fail) {
   __shared__ uint32_t s_ok;
   // The registration is the same for the whole workgroup: keep it in scalar registers.
-  const uint32_t X = __builtin_amdgcn_readfirstlane(L.groups);
-  const uint32_t k = __builtin_amdgcn_readfirstlane(L.k);
-  const uint32_t members = __builtin_amdgcn_readfirstlane(L.members);
-  const uint32_t xmask = __builtin_amdgcn_readfirstlane(L.xmask);
-  const uint32_t slot = __builtin_amdgcn_readfirstlane(L.slot);
-  const uint32_t fenced = __builtin_amdgcn_readfirstlane(L.fenced);
-  uint32_t* block = uniform_ptr(L.block);
-  Wait w(ctl, __builtin_amdgcn_readfirstlane(L.poll_sleep));
+  const uint32_t X = uniform(L.groups);
+  const uint32_t k = uniform(L.k);
+  const uint32_t members = uniform(L.members);
+  const uint32_t xmask = uniform(L.xmask);
+  const uint32_t slot = uniform(L.slot);
+  const uint32_t fenced = uniform(L.fenced);
+  uint8_t* block = reinterpret_cast<uint8_t*>(uniform_ptr(L.block));
+  // The populated XCDs' stamps: one line each, or packed in this CU's copy.
+  const uint32_t* stamps = uniform_ptr(L.stamps);
+  const uint32_t sstride = uniform(L.sstride);
+  Wait w(ctl, uniform(L.poll_sleep));
   int ok = 1;
   __syncthreads();
   if (threadIdx.x == 0) fail[(stamp + 1) & 1] = 0;  // for the next round's and_sync
-  const uint32_t C = __builtin_amdgcn_readfirstlane(L.copies);
+  const uint32_t C = uniform(L.copies);
   if (k == 0) {
     // XCD master: gather the XCD's arrivals, write the XCD's L2 back once, publish (in
     // every copy of the stamps, by the first wavefront after its writeback).
-    ok = scan_flags(block, kArriveWords, members, 0, stamp, w,
-                    __builtin_amdgcn_readfirstlane(L.lanes));
+    ok = scan_arrivals(block, members, stamp, w, uniform(L.lanes));
     ok = and_sync(ok, stamp, fail);
     if (!ok) return false;
-    if (C == 0) {
-      if (is_leader()) {
-        if (fenced) fence_release();
-        st_relaxed(uniform_ptr(L.xarrive_x), stamp);
-      }
-    } else if (threadIdx.x < 64) {
+    if (threadIdx.x < 64) {
       if (fenced) fence_release();
-      uint32_t* mail_x = uniform_ptr(L.mail_x);
-      for (uint32_t c = threadIdx.x; c < C; c += 64) st_relaxed(mail_x + pub[c], stamp);
+      if (C == 0) {
+        if (is_leader()) st_relaxed(uniform_ptr(L.xarrive_x), stamp);
+      } else {
+        uint32_t* mail_x = uniform_ptr(L.mail_x);
+        for (uint32_t c = threadIdx.x; c < C; c += 64) st_relaxed(mail_x + pub[c], stamp);
+      }
+      arrive_ahead(block, members, stamp + 1);
     }
   } else if (is_leader()) {
-    st_relaxed(block + (size_t)k * kArriveWords, stamp);
+    st_xcd8(block + k, (uint8_t)stamp);
   }
-  // The populated XCDs' stamps: one line each, or packed in this CU's copy.
-  const uint32_t* stamps = uniform_ptr(L.stamps);
-  const uint32_t sstride = __builtin_amdgcn_readfirstlane(L.sstride);
   if (!fenced) {
     // Coherent data: no cache maintenance, so nothing is shared per CU; every workgroup
     // polls the populated XCDs' stamps itself (two flag hops per round).
@@ -326,10 +357,7 @@ __device__ __forceinline__ bool xcd_wait(uint32_t stamp, const Ctl& ctl, const X
     __syncthreads();
     return true;
   }
-  if (is_leader()) {
-    ok = poll_until_cu(rel, stamp, w);
-    s_ok = ok;
-  }
+  if (is_leader()) s_ok = poll_until_cu(rel, stamp, w);
   __syncthreads();
   return s_ok;
 }
@@ -388,6 +416,8 @@ __device__ __forceinline__ bool xcd_setup(const BarrierState& s, const Ctl& ctl,
   for (uint32_t c = threadIdx.x; c < s.xcopies && c < kMaxCopies; c += blockDim.x)
     pub[c] = s.moff[c % X] + (c / X) * s.xmstep;
   __syncthreads();
+  if (L.k == 0 && threadIdx.x < 64)  // round 1 is stamp 2
+    arrive_ahead(reinterpret_cast<uint8_t*>(L.block), L.members, 2);
   return s_ok;
 }
 

@@ -123,7 +123,7 @@ namespace detail {
 
 __device__ __forceinline__ uint64_t cas_relaxed64(uint64_t* p, uint64_t expected,
                                                   uint64_t desired) {
-  __hip_atomic_compare_exchange_strong(p, &expected, desired, __ATOMIC_RELAXED,
+  __hip_atomic_compare_exchange_strong(as_global(p), &expected, desired, __ATOMIC_RELAXED,
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return expected;  // the value found
 }

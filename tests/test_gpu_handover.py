@@ -93,3 +93,23 @@ def test_default_mutex_lines(ctx, nwg, L, coherent):
     finally:
         g.close()
         m.close()
+
+
+@pytest.mark.parametrize("coherent", [0, 1])
+@pytest.mark.parametrize("nwg,lanes", [
+    (9, 64),        # XCDs with one member and with two
+    (504, 64), (512, 64), (520, 256),   # 63, 64 and 65 members: around a group of arrivals
+    (1032, 128),    # two groups and one member, two wavefronts
+    (2048, 64),     # four groups, one wavefront to scan them
+])
+def test_xcd_barrier_arrivals(ctx, nwg, lanes, coherent):
+    """The arrival bytes wrap every 256 rounds; a scan compares 64 members at a time."""
+    import paper_1110_4623_amd as sp
+    announce("xcd barrier", nwg, lanes, coherent)
+    b = sp.Barrier(ctx, "xcd", nwg, coherent_cs=coherent)
+    try:
+        chk, _ = b.run_hash(lanes, 700, 17)
+        assert b.info()["xcd_path"]
+    finally:
+        b.close()
+    assert (chk == oracle.barrier_closed(17, nwg, 700)).all()
