@@ -384,10 +384,11 @@ int sp_barrier_run_hash(sp_barrier* b, uint32_t lanes, uint32_t rounds, uint32_t
   // cooperative launches are not recorded: refuse before anything joins the capture
   const bool coop = b->kind == SP_BARRIER_GRID_SYNC || b->p.cooperative;
   if (coop && spi::capturing(s)) return SP_E_INVAL;
-  SP_CHECK(spi::fill_u32(ctx, b->d_state, b->state_words, 0, s));
-  SP_CHECK(spi::fill_u32(ctx, b->d_slots, 2ull * b->nwg, 0, s));
-  if (b->d_near) SP_CHECK(spi::fill_u32(ctx, b->d_near, b->near_words, 0, s));
-  SP_CHECK(spi::begin_timed(ctx, s));
+  spi::Resets z;
+  z.add(b->d_state, b->state_words);
+  z.add(b->d_slots, 2ull * b->nwg);
+  if (b->d_near) z.add(b->d_near, b->near_words);
+  SP_CHECK(spi::begin_timed(ctx, s, z));
   uint64_t timeout = spi::timeout_ticks(ctx, b->p);
   uint32_t N = b->nwg;
   if (b->kind == SP_BARRIER_GRID_SYNC) {  // grid.sync() requires a cooperative launch

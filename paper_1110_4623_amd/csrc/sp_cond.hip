@@ -94,24 +94,35 @@ __global__ SP_FULL_OCCUPANCY void k_bounded_buffer(sp::MutexState m, sp::CondSta
 // out[0] = xor of taken values, out[1] = sum, out[2] = values taken, out[3] = values put,
 // out[4] = most values ever in the buffer, out[5] = values left in it.
 __global__ void k_bb_reduce(const unsigned long long* res, uint32_t nwg, uint32_t producers,
-                            const uint32_t* bstate, unsigned long long* out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  unsigned long long x = 0, s = 0, taken = 0, put = 0;
-  for (uint32_t b = 0; b < nwg; ++b) {
+                            const uint32_t* bstate, unsigned long long* out,
+                            const uint32_t* err, uint32_t* h_err) {
+  // one workgroup of four wavefronts: every lane takes a share of the records, then the
+  // lanes' sums meet in the wavefront and the wavefronts' in LDS
+  __shared__ unsigned long long w[4][4];
+  unsigned long long v[4] = {0, 0, 0, 0};  // xor, sum, taken, put
+  for (uint32_t b = threadIdx.x; b < nwg; b += blockDim.x) {
+    const unsigned long long* r = res + 4 * (size_t)b;
     if (b < producers) {
-      put += res[4 * (size_t)b + 2];
+      v[3] += r[2];
     } else {
-      x ^= res[4 * (size_t)b + 0];
-      s += res[4 * (size_t)b + 1];
-      taken += res[4 * (size_t)b + 2];
+      v[0] ^= r[0];
+      v[1] += r[1];
+      v[2] += r[2];
     }
   }
-  out[0] = x;
-  out[1] = s;
-  out[2] = taken;
-  out[3] = put;
+  for (int off = 32; off > 0; off >>= 1) {
+    v[0] ^= __shfl_down(v[0], off, 64);
+    for (int i = 1; i < 4; ++i) v[i] += __shfl_down(v[i], off, 64);
+  }
+  if ((threadIdx.x & 63) == 0)
+    for (int i = 0; i < 4; ++i) w[threadIdx.x >> 6][i] = v[i];
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  out[0] = w[0][0] ^ w[1][0] ^ w[2][0] ^ w[3][0];
+  for (int i = 1; i < 4; ++i) out[i] = w[0][i] + w[1][i] + w[2][i] + w[3][i];
   out[4] = bstate[B_MAX * kLine];
   out[5] = bstate[B_COUNT * kLine];
+  spi::report_error(err, h_err);
 }
 
 const void* bb_kernel(uint32_t kind) {
@@ -212,20 +223,18 @@ int bb_run(sp_ctx* ctx, uint32_t mutex_kind, uint32_t nwg, uint32_t producers, u
   uint64_t off = (uint64_t)(buf + capacity - base);
   off = (off + 1) & ~1ull;
   unsigned long long* res = reinterpret_cast<unsigned long long*>(base + off);
-  SP_CHECK(spi::fill_u32(ctx, base, L.total, 0, s));
-  SP_CHECK(spi::begin_timed(ctx, s));
+  spi::Resets z;
+  z.add(base, L.total);
+  SP_CHECK(spi::begin_timed(ctx, s, z));
   uint64_t timeout = spi::timeout_ticks(ctx, q);
   unsigned long long* resp = res;
   void* args[] = {&ms, &nf, &ne, &bstate, &buf, &capacity, &producers, &items, &seed, &resp,
                   &out_taken, &ctx->d_err, &timeout};
   SP_HIP(ctx, hipLaunchKernel(kern, dim3(nwg), dim3(lanes), args, 0, s));
-  int rc = spi::end_timed(ctx, s, st, nwg, lanes, per_cu, items);
-  hipLaunchKernelGGL(k_bb_reduce, dim3(1), dim3(64), 0, s, res, nwg, producers, bstate,
-                     reinterpret_cast<unsigned long long*>(out));
-  const hipError_t launch = hipGetLastError();
-  SP_CHECK(spi::sync_unless_capturing(ctx, s));
-  SP_HIP(ctx, launch);
-  return rc;
+  SP_CHECK(spi::mark_end(ctx, s));
+  hipLaunchKernelGGL(k_bb_reduce, dim3(1), dim3(256), 0, s, res, nwg, producers, bstate,
+                     reinterpret_cast<unsigned long long*>(out), ctx->d_err, ctx->h_err);
+  return spi::wait_done(ctx, s, st, nwg, lanes, per_cu, items);
 }
 
 }  // namespace

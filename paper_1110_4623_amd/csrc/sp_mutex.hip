@@ -69,11 +69,13 @@ __global__ SP_FULL_OCCUPANCY void k_mutex(sp::MutexState s, uint32_t nlocks, uin
 }
 
 __global__ void k_gather_words(const uint32_t* words, uint32_t nlocks, uint32_t W,
-                               uint32_t wstride, uint32_t* out) {
+                               uint32_t wstride, uint32_t* out, const uint32_t* err,
+                               uint32_t* h_err) {
   const uint64_t n = (uint64_t)nlocks * W;
   for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
        i += (uint64_t)gridDim.x * blockDim.x)
     out[i] = words[(i / W) * wstride + i % W];
+  if (blockIdx.x == 0 && threadIdx.x == 0) spi::report_error(err, h_err);
 }
 
 template <bool FENCED>
@@ -225,6 +227,7 @@ int sp_mutex_run(sp_mutex* m, uint32_t nwg, uint32_t lanes, uint64_t total_acq,
   ms.qstride = 1;
   ms.cohort_bound = q.cohort_passes;
   ms.cuq = nullptr;
+  spi::Resets z;
   if (kind == SP_MUTEX_RING || kind == SP_MUTEX_ARRAY || kind == SP_MUTEX_COHORT ||
       kind == SP_MUTEX_MCS || kind == SP_MUTEX_CU_COHORT) {
     // The ring needs a slot per contender (each workgroup has at most one arrival
@@ -256,25 +259,22 @@ int sp_mutex_run(sp_mutex* m, uint32_t nwg, uint32_t lanes, uint64_t total_acq,
     ms.queue = m->d_queue;
     if (kind == SP_MUTEX_CU_COHORT)  // the CU cohorts' lines follow the XCD cohorts'
       ms.cuq = ms.queue + (uint64_t)m->nlocks * sp::kCohortLines * sp::kXccSlots * ms.qstride;
-    SP_CHECK(spi::fill_u32(ctx, m->d_queue, words, 0, s));
+    z.add(m->d_queue, words);
   }
-  SP_CHECK(spi::fill_u32(ctx, m->d_state, m->state_words, 0, s));
-  SP_CHECK(spi::fill_u32(ctx, m->d_words, (uint64_t)m->nlocks * m->wstride, 0, s));
+  z.add(m->d_state, m->state_words);
+  z.add(m->d_words, (uint64_t)m->nlocks * m->wstride);
   uint32_t per_cu = 0;
   SP_CHECK(spi::resident_per_cu(ctx, kern, lanes, &per_cu));
-  SP_CHECK(spi::begin_timed(ctx, s));
+  SP_CHECK(spi::begin_timed(ctx, s, z));
   uint64_t timeout = spi::timeout_ticks(ctx, q);
   uint32_t nlocks = m->nlocks, W = m->W, wstride = m->wstride;
   void* args[] = {&ms, &nlocks, &W, &wstride, &m->d_words, &nwg, &total_acq, &max_delay_cyc,
                   &seed, &out_finish, &owner, &ctx->d_err, &timeout};
   SP_HIP(ctx, hipLaunchKernel(kern, dim3(nwg), dim3(lanes), args, 0, s));
-  int rc = spi::end_timed(ctx, s, st, nwg, lanes, (uint32_t)per_cu, total_acq);
-  if (rc != SP_OK && rc != SP_E_TIMEOUT && rc != SP_E_PARITY) return rc;
+  SP_CHECK(spi::mark_end(ctx, s));
   hipLaunchKernelGGL(k_gather_words, dim3(256), dim3(256), 0, s, m->d_words, nlocks, W, wstride,
-                     out_words);
-  SP_HIP(ctx, hipGetLastError());
-  SP_CHECK(spi::sync_unless_capturing(ctx, s));
-  return rc;
+                     out_words, ctx->d_err, ctx->h_err);
+  return spi::wait_done(ctx, s, st, nwg, lanes, (uint32_t)per_cu, total_acq);
 }
 
 }  // extern "C"

@@ -131,8 +131,10 @@ __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_
 
 __global__ void k_sem_state(const uint32_t* state, uint32_t stride, uint32_t alg4,
                             const uint32_t* cq, uint32_t cq_stride, uint32_t cq_len,
-                            const uint32_t* arr, uint32_t nq, uint32_t* out) {
+                            const uint32_t* arr, uint32_t nq, uint32_t* out,
+                            const uint32_t* err, uint32_t* h_err) {
   if (threadIdx.x == 0) {
+    spi::report_error(err, h_err);
     // cohort kind: local tickets drawn but never served, over the queues in use (0 at rest)
     uint32_t unserved = 0;
     if (cq)
@@ -306,39 +308,37 @@ int sp_sem_run(sp_sem* sem, uint32_t nwg, uint32_t lanes, uint64_t total_pairs,
   const bool queued = kind == SP_SEM_COHORT || kind == SP_SEM_ARRAY || kind == SP_SEM_CHAIN ||
                       kind == SP_SEM_XCD_CHAIN || kind == SP_SEM_CU_LOCK;
   if (queued && !sem->d_cq) return SP_E_INVAL;
-  SP_CHECK(spi::fill_u32(ctx, base, sem->state_words, 0, s));
+  const uint32_t alg4 = kind == SP_SEM_SPIN || kind == SP_SEM_SPIN_BACKOFF;
+  spi::Resets z;
+  z.add(ss.S, 1, alg4 ? sem->K + 1 : 0);  // Algorithm 4: S = K + 1
+  z.add(base + L_S * sw + 1, (uint64_t)L_LINES * sw - 1);
   // the queues a run uses: one per XCD (cohort, per-XCD chains) or queue 0 (array, chain)
   const uint32_t nq = kind == SP_SEM_ARRAY || kind == SP_SEM_CHAIN ? 1u : ss.cq_n;
   const uint64_t cu_lock_lines =
       (uint64_t)sp::kXccSlots * (sp::kCohortLines + sp::kCuIds * sp::kCuLines);
   const uint64_t qwords = kind == SP_SEM_CU_LOCK ? cu_lock_lines * sem->cq_stride
                                                  : (uint64_t)nq * (2 + kCohortSlots) * sem->cq_stride;
-  if (queued) SP_CHECK(spi::fill_u32(ctx, sem->d_cq, qwords, 0, s));
+  if (queued) z.add(sem->d_cq, qwords);
   if (out_data) {
-    SP_CHECK(spi::fill_u32(ctx, out_data, sem->K, 0, s));
-    if (sem->K > 1) SP_CHECK(spi::fill_u32(ctx, sem->d_owner, (uint64_t)sem->K * kOwnerWords, 0, s));
+    z.add(out_data, sem->K);
+    if (sem->K > 1) z.add(sem->d_owner, (uint64_t)sem->K * kOwnerWords);
   }
   uint32_t* owner = sem->d_owner;
-  if (kind == SP_SEM_SPIN || kind == SP_SEM_SPIN_BACKOFF)
-    SP_CHECK(spi::fill_u32(ctx, ss.S, 1, sem->K + 1, s));  // Algorithm 4: S = K + 1
   uint32_t per_cu = 0;
   SP_CHECK(spi::resident_per_cu(ctx, kern, lanes, &per_cu));
-  SP_CHECK(spi::begin_timed(ctx, s));
+  SP_CHECK(spi::begin_timed(ctx, s, z));
   uint64_t timeout = spi::timeout_ticks(ctx, q);
   uint32_t stride = sw;
   void* args[] = {&ss, &stride, &base, &nwg, &total_pairs, &max_hold_cyc, &seed, &track,
                   &out_chk, &out_data, &owner, &ctx->d_err, &timeout};
   SP_HIP(ctx, hipLaunchKernel(kern, dim3(nwg), dim3(lanes), args, 0, s));
-  int rc = spi::end_timed(ctx, s, st, nwg, lanes, (uint32_t)per_cu, total_pairs);
-  const uint32_t alg4 = kind == SP_SEM_SPIN || kind == SP_SEM_SPIN_BACKOFF;
+  SP_CHECK(spi::mark_end(ctx, s));
   const uint32_t* cq = kind == SP_SEM_COHORT ? sem->d_cq : nullptr;
   const uint32_t* arr = kind == SP_SEM_ARRAY || kind == SP_SEM_CHAIN || kind == SP_SEM_XCD_CHAIN
                             ? sem->d_cq : nullptr;
   hipLaunchKernelGGL(k_sem_state, dim3(1), dim3(64), 0, s, base, sw, alg4, cq, sem->cq_stride,
-                     kCohortSlots, arr, queued ? nq : 0u, out_state);
-  SP_HIP(ctx, hipGetLastError());
-  SP_CHECK(spi::sync_unless_capturing(ctx, s));
-  return rc;
+                     kCohortSlots, arr, queued ? nq : 0u, out_state, ctx->d_err, ctx->h_err);
+  return spi::wait_done(ctx, s, st, nwg, lanes, (uint32_t)per_cu, total_pairs);
 }
 
 }  // extern "C"
