@@ -5,10 +5,24 @@
 
 namespace {
 
-__global__ void k_fill_u32(uint32_t* d, uint64_t n, uint32_t v) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * blockDim.x)
-    d[i] = v;
+// Every range with 16-byte stores between its aligned ends.
+__global__ void k_reset(spi::Resets z) {
+  const uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+  const uint64_t g = (uint64_t)gridDim.x * blockDim.x;
+  for (uint32_t k = 0; k < z.n; ++k) {
+    const auto& r = z.r[k];
+    const uint64_t lead = std::min<uint64_t>((4 - ((uintptr_t)r.p / 4) % 4) % 4, r.words);
+    const uint64_t n16 = (r.words - lead) / 4, tail = lead + n16 * 4;
+    uint4* q = reinterpret_cast<uint4*>(r.p + lead);
+    for (uint64_t i = t; i < n16; i += g) q[i] = make_uint4(r.value, r.value, r.value, r.value);
+    if (t < lead) r.p[t] = r.value;
+    if (t < r.words - tail) r.p[tail + t] = r.value;
+  }
+}
+
+// A run's last kernel where it has none of its own.
+__global__ void k_finish(const uint32_t* err, uint32_t* h_err) {
+  if (threadIdx.x == 0) spi::report_error(err, h_err);
 }
 
 __global__ void k_probe_xcc(uint32_t* out) {
@@ -40,15 +54,29 @@ int normalize(const sp_ctx* ctx, const sp_params* in, sp_params* out) {
   return SP_OK;
 }
 
-int fill_u32(sp_ctx* ctx, uint32_t* d, uint64_t words, uint32_t value, hipStream_t s) {
-  if (words == 0) return SP_OK;
-  uint64_t blocks = std::min<uint64_t>((words + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_fill_u32, dim3((uint32_t)blocks), dim3(256), 0, s, d, words, value);
+int reset(sp_ctx* ctx, const Resets& z, hipStream_t s) {
+  uint64_t most = 0;
+  for (uint32_t k = 0; k < z.n; ++k) most = std::max(most, z.r[k].words);
+  if (most == 0) return SP_OK;
+  const uint64_t blocks = std::min<uint64_t>((most + 1023) / 1024, 4096);
+  hipLaunchKernelGGL(k_reset, dim3((uint32_t)blocks), dim3(256), 0, s, z);
   SP_HIP(ctx, hipGetLastError());
   return SP_OK;
 }
 
+int fill_u32(sp_ctx* ctx, uint32_t* d, uint64_t words, uint32_t value, hipStream_t s) {
+  Resets z;
+  z.add(d, words, value);
+  return reset(ctx, z, s);
+}
+
 int resident_per_cu(sp_ctx* ctx, const void* kern, uint32_t lanes, uint32_t* per_cu) {
+  std::lock_guard<std::mutex> hold(ctx->occupancy_mu);
+  for (const auto& o : ctx->occupancy)
+    if (o.kern == kern && o.lanes == lanes) {
+      *per_cu = o.per_cu;
+      return SP_OK;
+    }
   int rt = 0;
   SP_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&rt, kern, (int)lanes, 0));
   hipFuncAttributes fa{};
@@ -59,6 +87,7 @@ int resident_per_cu(sp_ctx* ctx, const void* kern, uint32_t lanes, uint32_t* per
   occ.lds_bytes = (uint32_t)fa.sharedSizeBytes;
   occ.lanes = lanes;
   *per_cu = sp_resident_per_cu(&occ);
+  ctx->occupancy.push_back({kern, lanes, *per_cu});
   return SP_OK;
 }
 
@@ -73,31 +102,31 @@ int sync_unless_capturing(sp_ctx* ctx, hipStream_t s) {
   return SP_OK;
 }
 
-int begin_timed(sp_ctx* ctx, hipStream_t s) {
+int begin_timed(sp_ctx* ctx, hipStream_t s, Resets z) {
   if (!usable(ctx)) return SP_E_INVAL;
-  // Under capture the graph's launcher clears the watchdog word once per replay and
-  // times the replays; the recorded call adds only its own kernels.
-  if (capturing(s)) return SP_OK;
-  SP_CHECK(fill_u32(ctx, ctx->d_err, 1, 0, s));
-  SP_HIP(ctx, hipEventRecord(ctx->ev0, s));
+  const bool recording = capturing(s);
+  if (!recording) z.add(ctx->d_err, 1);
+  SP_CHECK(reset(ctx, z, s));
+  if (!recording) SP_HIP(ctx, hipEventRecord(ctx->ev0, s));
   return SP_OK;
 }
 
-int end_timed(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
+int mark_end(sp_ctx* ctx, hipStream_t s) {
+  SP_HIP(ctx, hipGetLastError());
+  if (!capturing(s)) SP_HIP(ctx, hipEventRecord(ctx->ev1, s));
+  return SP_OK;
+}
+
+int wait_done(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
               uint32_t resident_per_cu, uint64_t ops) {
   SP_HIP(ctx, hipGetLastError());
-  if (capturing(s)) {
-    if (st) memset(st, 0, sizeof(*st));
-    return SP_OK;
-  }
-  SP_HIP(ctx, hipEventRecord(ctx->ev1, s));
+  if (st) memset(st, 0, sizeof(*st));
+  if (capturing(s)) return SP_OK;
   SP_HIP(ctx, hipStreamSynchronize(s));
   float ms = 0.f;
   SP_HIP(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
-  uint32_t err = 0;
-  SP_HIP(ctx, hipMemcpy(&err, ctx->d_err, sizeof(err), hipMemcpyDeviceToHost));
+  const uint32_t err = __atomic_load_n(ctx->h_err, __ATOMIC_ACQUIRE);
   if (st) {
-    memset(st, 0, sizeof(*st));
     st->kernel_ms = ms;
     st->nwg = nwg;
     st->lanes = lanes;
@@ -108,6 +137,13 @@ int end_timed(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t l
   if (err == sp::DEV_TIMEOUT) return SP_E_TIMEOUT;
   if (err != sp::DEV_OK) return SP_E_PARITY;
   return SP_OK;
+}
+
+int end_timed(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
+              uint32_t resident_per_cu, uint64_t ops) {
+  SP_CHECK(mark_end(ctx, s));
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, s, ctx->d_err, ctx->h_err);
+  return wait_done(ctx, s, st, nwg, lanes, resident_per_cu, ops);
 }
 
 }  // namespace spi
@@ -182,6 +218,10 @@ int sp_init(int device, sp_ctx** out) {
     ctx->wall_khz = (uint32_t)khz;
   if ((e = hipMalloc(&ctx->d_err, 256)) != hipSuccess) return fail(e);
   if ((e = hipMalloc(&ctx->d_scratch, 4096)) != hipSuccess) return fail(e);
+  if ((e = hipHostMalloc((void**)&ctx->h_err, 4096,
+                         hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess)
+    return fail(e);
+  *ctx->h_err = sp::DEV_OK;
   if ((e = hipEventCreate(&ctx->ev0)) != hipSuccess) return fail(e);
   if ((e = hipEventCreate(&ctx->ev1)) != hipSuccess) return fail(e);
   if ((e = hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking)) != hipSuccess)
@@ -259,11 +299,12 @@ int sp_fini(sp_ctx* ctx) {
   (void)hipStreamDestroy(ctx->capture_stream);
   (void)hipEventDestroy(ctx->ev1);
   (void)hipEventDestroy(ctx->ev0);
+  (void)hipHostFree(ctx->h_err);
   (void)hipFree(ctx->d_scratch);
   (void)hipFree(ctx->d_err);
   ctx->capture_stream = ctx->setup_stream = nullptr;
   ctx->ev0 = ctx->ev1 = nullptr;
-  ctx->d_err = ctx->d_scratch = nullptr;
+  ctx->d_err = ctx->d_scratch = ctx->h_err = nullptr;
   ctx->closed = true;
   if (ctx->refs == 0) delete ctx;
   return SP_OK;

@@ -5,6 +5,8 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <mutex>
+#include <vector>
 
 #include "sp.h"
 #include "sp/atomics.hpp"
@@ -30,6 +32,11 @@ struct sp_ctx {
   uint32_t xcc_mask = 0;  // XCC ids seen at sp_init (bit i = id i)
   uint32_t wall_khz = 100000;
   uint32_t* d_err = nullptr;   // watchdog word, own 256-byte block
+  uint32_t* h_err = nullptr;   // pinned: the watchdog word as a run's last kernel found it
+  // occupancy of the library's kernels, asked of the runtime once per kernel and size
+  struct Occupancy { const void* kern; uint32_t lanes, per_cu; };
+  std::vector<Occupancy> occupancy;
+  std::mutex occupancy_mu;
   uint32_t* d_scratch = nullptr;  // small staging area (4 KiB) for state readback
   // the allocation-free entry point's fixed workspace on this device (a file-scope device
   // array; its address is looked up once per device at sp_init)
@@ -95,7 +102,22 @@ inline sp::BackoffCfg backoff_cfg(const sp_params& p, uint32_t* private_word) {
   return c;
 }
 
-// Zero `words` uint32 at d with a kernel (no memset nodes, so launches stay capturable).
+// Up to kMax ranges of uint32 words set by one kernel (no memset nodes, so launches stay
+// capturable): what a run has to reset costs one launch, not one per array.
+struct Resets {
+  static constexpr uint32_t kMax = 8;
+  struct Range {
+    uint32_t* p;
+    uint64_t words;
+    uint32_t value;
+  } r[kMax];
+  uint32_t n = 0;
+  void add(void* p, uint64_t words, uint32_t value = 0) {
+    if (words) r[n++] = Range{static_cast<uint32_t*>(p), words, value};
+  }
+};
+int reset(sp_ctx* ctx, const Resets& z, hipStream_t s);
+// One range.
 int fill_u32(sp_ctx* ctx, uint32_t* d, uint64_t words, uint32_t value, hipStream_t s);
 
 // True while `s` is being captured into a HIP graph (sp_graph_begin): run calls then
@@ -104,13 +126,26 @@ bool capturing(hipStream_t s);
 // hipStreamSynchronize(s), or nothing while `s` is being captured.
 int sync_unless_capturing(sp_ctx* ctx, hipStream_t s);
 
-// Clears the watchdog word, records ev0 (nothing under capture).
-int begin_timed(sp_ctx* ctx, hipStream_t s);
-// Records ev1, waits for the stream, reads the watchdog word, fills st (under capture:
-// zeroes st and returns SP_OK).
+// Around a run's main kernel.  begin_timed resets `z` and the watchdog word and records
+// ev0; mark_end records ev1; the run's last kernel (its own, or end_timed's) copies the
+// watchdog word into h_err (report_error); wait_done waits for the stream once, reads the
+// time and h_err and fills st.  Under capture nothing is timed, awaited or read: the graph's
+// launcher does that, and clears the watchdog word, once per replay.
+// What bounds a small run is the number of launches and waits around its kernel: on an
+// MI355X a mutex run of 24 workgroups took 135-137 us from call to words with a fill kernel
+// per array, a copy of the watchdog word and a second wait for the gather, 115 us with one
+// reset kernel, the watchdog word in pinned memory and one wait.
+int begin_timed(sp_ctx* ctx, hipStream_t s, Resets z = Resets());
+int mark_end(sp_ctx* ctx, hipStream_t s);
+int wait_done(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
+              uint32_t resident_per_cu, uint64_t ops);
+// mark_end, a one-lane kernel that reports the watchdog word, wait_done.
 int end_timed(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
               uint32_t resident_per_cu, uint64_t ops);
-
+__device__ __forceinline__ void report_error(const uint32_t* err, uint32_t* h_err) {
+  __hip_atomic_store(h_err, __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // Workgroups of `kern` (launched with `lanes` threads) that fit on one CU at once: the
 // runtime's occupancy figure checked against the kernel's own VGPR and LDS use
 // (sp_resident_per_cu).

@@ -113,3 +113,44 @@ def test_xcd_barrier_arrivals(ctx, nwg, lanes, coherent):
     finally:
         b.close()
     assert (chk == oracle.barrier_closed(17, nwg, 700)).all()
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+@pytest.mark.parametrize("K", [1, 2, 3, 5, 301])
+def test_resets_reach_their_range_and_no_more(ctx, K, offset):
+    """A run resets its arrays with 16-byte stores between their aligned ends: an output of
+    K words at any word offset is reset whole, and its neighbours keep their values."""
+    import ctypes
+
+    import paper_1110_4623_amd as sp
+    from paper_1110_4623_amd import _native as N
+    if ctx.torch is None:
+        pytest.skip("needs torch's device tensors")
+    announce("resets", K, offset)
+    s = sp.Semaphore(ctx, "sleep", K)
+    out = ctx.torch.full((K + 16,), 77, dtype=ctx.torch.int32, device="cuda")
+    chk, state, st = ctx.zeros(64), ctx.zeros(8), N.Stats()
+    try:
+        for total in (1000, 500):  # the second run finds the first one's words
+            rc = N.lib.sp_sem_run(s.h, 64, 64, total, 0, 5, 0, ctx.ptr(chk), ctx.ptr(state),
+                                  ctypes.c_void_p(out.data_ptr() + 4 * (4 + offset)),
+                                  ctypes.byref(st), ctx.stream())
+            assert rc == 0 and st.device_error == 0 and st.kernel_ms > 0
+            got = out.cpu().numpy()
+            assert got[4 + offset:4 + offset + K].sum() == total
+            assert (got[:4 + offset] == 77).all() and (got[4 + offset + K:] == 77).all()
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("nwg,producers", [(2, 1), (257, 1), (300, 299), (1024, 512)])
+def test_ring_totals_over_all_workgroups(ctx, nwg, producers):
+    """The totals of more and of fewer workgroups than the adding kernel has lanes."""
+    import numpy as np
+
+    import paper_1110_4623_amd as sp
+    announce("ring totals", nwg, producers)
+    r = sp.bounded_buffer(ctx, "array", nwg, producers, 32, 3001, 7, values=True)
+    assert r["taken"] == r["put"] == 3001 and r["left"] == 0 and 1 <= r["max_count"] <= 32
+    assert r["sum"] == int(r["values"].astype(np.uint64).sum())
+    assert r["xor"] == int(np.bitwise_xor.reduce(r["values"]))
