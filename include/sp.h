@@ -310,10 +310,15 @@ uint32_t sp_resident_per_cu(const sp_occupancy* occ);
 /* ---- device memory for callers without their own allocator ------------------------
  * sp_buffer_alloc: `bytes` of device memory on the context's GPU, zero-filled; the
  * caller frees it with sp_buffer_free.  sp_buffer_read / sp_buffer_write copy between
- * a device buffer and host memory (synchronous).  Errors: SP_E_INVAL, SP_E_HIP.          */
+ * a device buffer and host memory (synchronous).  Errors: SP_E_INVAL, SP_E_HIP.
+ * sp_buffer_read_strided: host_dst[i] = the uint32 at dev_src + i * stride_bytes (a
+ * multiple of 4), i < count, after the work already on `stream`; only those words cross
+ * to the host.  Not under graph capture (SP_E_INVAL).                                    */
 int sp_buffer_alloc(sp_ctx* ctx, uint64_t bytes, void** out);
 int sp_buffer_free(sp_ctx* ctx, void* p);
 int sp_buffer_read(sp_ctx* ctx, void* host_dst, const void* dev_src, uint64_t bytes);
+int sp_buffer_read_strided(sp_ctx* ctx, uint32_t* host_dst, const uint32_t* dev_src,
+                           uint64_t count, uint64_t stride_bytes, void* stream);
 int sp_buffer_write(sp_ctx* ctx, void* dev_dst, const void* host_src, uint64_t bytes);
 
 /* ---- barrier (Section 5, Barrier; Table 4 Barrier()) ------------------------------------

@@ -190,6 +190,7 @@ def _load():
         "sp_buffer_alloc": (i32, [vp, u64, P(vp)]),
         "sp_buffer_free": (i32, [vp, vp]),
         "sp_buffer_read": (i32, [vp, vp, vp, u64]),
+        "sp_buffer_read_strided": (i32, [vp, vp, vp, u64, u64, vp]),
         "sp_buffer_write": (i32, [vp, vp, vp, u64]),
         "sp_barrier_create": (i32, [vp, u32, u32, P(Params), P(vp)]),
         "sp_barrier_destroy": (i32, [vp]),

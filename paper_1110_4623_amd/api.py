@@ -138,6 +138,23 @@ class Context:
         a = a.view(np.uint64) if dtype == "u64" and a.dtype == np.int64 else a
         return (a if count is None else a[:count]).astype(npdt, copy=False)
 
+    def _read_strided(self, buf, count: int, stride: int) -> np.ndarray:
+        """The first uint32 word of each of `count` records `stride` bytes apart.  Only those
+        words cross to the host: of 2^20 words 64 bytes apart 4 MB instead of 64."""
+        words = count * stride // 4
+        if isinstance(buf, DeviceBuffer):
+            fits, s = buf.nbytes >= 4 * words, ctypes.c_void_p(0)
+        else:
+            fits = buf.dtype == self.torch.int32 and buf.numel() >= words
+            s = ctypes.c_void_p(self.torch.cuda.current_stream().cuda_stream)
+        if not fits:
+            return self.read(buf, "u32", words).reshape(count, stride // 4)[:, 0].copy()
+        out = np.empty(count, np.uint32)
+        check(lib.sp_buffer_read_strided(self.h, out.ctypes.data_as(ctypes.c_void_p),
+                                         self.ptr(buf), count, stride, s),
+              "sp_buffer_read_strided", self.h)
+        return out
+
     @staticmethod
     def ptr(buf) -> ctypes.c_void_p:
         if buf is None:
@@ -448,7 +465,7 @@ def bench_atomic(ctx: Context, op: str, nwg: int, lanes: int, T: int, stride: in
     check(lib.sp_bench_atomic(ctx.h, N.OPS[op], nwg, lanes, T, stride, N.ISSUE[mode], n,
                               seed & 0xFFFFFFFF, ctx.ptr(perm), ctx.ptr(buf), ctx.ptr(out),
                               ctypes.byref(st), ctx.stream()), "sp_bench_atomic", ctx.h)
-    finals = ctx.read(buf, "u32", words).reshape(T, stride // 4)[:, 0].copy()
+    finals = ctx._read_strided(buf, T, stride)
     return finals, int(ctx.read(out, "u64", 1)[0]), st.as_dict()
 
 

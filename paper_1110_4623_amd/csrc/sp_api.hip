@@ -20,6 +20,18 @@ __global__ void k_reset(spi::Resets z) {
   }
 }
 
+// Words of pinned staging (4 MiB): what one wait for a strided read brings.
+constexpr uint64_t kStageWords = 1 << 20;
+
+// out[i] = word i * stride_words, i < n; out may be pinned host memory (whole lines of it
+// leave each wavefront).
+__global__ void k_gather_strided(const uint32_t* src, uint64_t n, uint64_t stride_words,
+                                 uint32_t* out) {
+  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
+       i += (uint64_t)gridDim.x * blockDim.x)
+    out[i] = __builtin_nontemporal_load(&src[i * stride_words]);
+}
+
 // A run's last kernel where it has none of its own.
 __global__ void k_finish(const uint32_t* err, uint32_t* h_err) {
   if (threadIdx.x == 0) spi::report_error(err, h_err);
@@ -299,12 +311,13 @@ int sp_fini(sp_ctx* ctx) {
   (void)hipStreamDestroy(ctx->capture_stream);
   (void)hipEventDestroy(ctx->ev1);
   (void)hipEventDestroy(ctx->ev0);
+  (void)hipHostFree(ctx->h_stage);
   (void)hipHostFree(ctx->h_err);
   (void)hipFree(ctx->d_scratch);
   (void)hipFree(ctx->d_err);
   ctx->capture_stream = ctx->setup_stream = nullptr;
   ctx->ev0 = ctx->ev1 = nullptr;
-  ctx->d_err = ctx->d_scratch = ctx->h_err = nullptr;
+  ctx->d_err = ctx->d_scratch = ctx->h_err = ctx->h_stage = nullptr;
   ctx->closed = true;
   if (ctx->refs == 0) delete ctx;
   return SP_OK;
@@ -382,6 +395,29 @@ int sp_buffer_read(sp_ctx* ctx, void* host_dst, const void* dev_src, uint64_t by
   if (!usable(ctx) || !host_dst || !dev_src) return SP_E_INVAL;
   SP_HIP(ctx, hipSetDevice(ctx->device));
   SP_HIP(ctx, hipMemcpy(host_dst, dev_src, bytes, hipMemcpyDeviceToHost));
+  return SP_OK;
+}
+
+int sp_buffer_read_strided(sp_ctx* ctx, uint32_t* host_dst, const uint32_t* dev_src,
+                           uint64_t count, uint64_t stride_bytes, void* stream) {
+  if (!usable(ctx) || !host_dst || !dev_src || stride_bytes == 0 || stride_bytes % 4)
+    return SP_E_INVAL;
+  hipStream_t s = spi::as_stream(stream);
+  if (spi::capturing(s)) return SP_E_INVAL;
+  SP_HIP(ctx, hipSetDevice(ctx->device));
+  std::lock_guard<std::mutex> hold(ctx->stage_mu);
+  if (!ctx->h_stage)
+    SP_HIP(ctx, hipHostMalloc((void**)&ctx->h_stage, kStageWords * sizeof(uint32_t),
+                              hipHostMallocMapped));
+  for (uint64_t at = 0; at < count; at += kStageWords) {
+    const uint64_t n = std::min<uint64_t>(count - at, kStageWords);
+    hipLaunchKernelGGL(k_gather_strided, dim3((uint32_t)std::min<uint64_t>((n + 255) / 256, 4096)),
+                       dim3(256), 0, s, dev_src + at * (stride_bytes / 4), n, stride_bytes / 4,
+                       ctx->h_stage);
+    SP_HIP(ctx, hipGetLastError());
+    SP_HIP(ctx, hipStreamSynchronize(s));
+    memcpy(host_dst + at, ctx->h_stage, n * sizeof(uint32_t));
+  }
   return SP_OK;
 }
 

@@ -33,6 +33,9 @@ struct sp_ctx {
   uint32_t wall_khz = 100000;
   uint32_t* d_err = nullptr;   // watchdog word, own 256-byte block
   uint32_t* h_err = nullptr;   // pinned: the watchdog word as a run's last kernel found it
+  // pinned staging of sp_buffer_read_strided, made by its first call
+  uint32_t* h_stage = nullptr;
+  std::mutex stage_mu;
   // occupancy of the library's kernels, asked of the runtime once per kernel and size
   struct Occupancy { const void* kern; uint32_t lanes, per_cu; };
   std::vector<Occupancy> occupancy;

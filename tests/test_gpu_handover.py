@@ -154,3 +154,22 @@ def test_ring_totals_over_all_workgroups(ctx, nwg, producers):
     assert r["taken"] == r["put"] == 3001 and r["left"] == 0 and 1 <= r["max_count"] <= 32
     assert r["sum"] == int(r["values"].astype(np.uint64).sum())
     assert r["xor"] == int(np.bitwise_xor.reduce(r["values"]))
+
+
+@pytest.mark.parametrize("T,stride", [(1, 4), (255, 4), (1000, 64), (1 << 20, 4),
+                                      ((1 << 20) + 1, 8), ((2 << 20) + 77, 12)])
+def test_finals_of_strided_words(ctx, T, stride):
+    """Final words read through the staging: none, one and several times its size, on a
+    fresh and on a caller's buffer."""
+    import numpy as np
+
+    import paper_1110_4623_amd as sp
+    import sp_inputs
+    announce("strided finals", T, stride)
+    perm = sp_inputs.permutation(T, 3)
+    buf = ctx.zeros(T * stride // 4 + 5)
+    for b in (None, buf):
+        finals, _, _ = sp.bench_atomic(ctx, "add", 16, 64, T, stride, "per_lane", 3, 3, perm, b)
+        pos = (np.arange(16 * 64)[:, None] + np.arange(3)[None, :]) % T
+        want = np.bincount(perm[pos].ravel(), minlength=T).astype(np.uint32)
+        assert finals.dtype == np.uint32 and (finals == want).all()
