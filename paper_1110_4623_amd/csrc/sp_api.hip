@@ -32,9 +32,20 @@ __global__ void k_gather_strided(const uint32_t* src, uint64_t n, uint64_t strid
     out[i] = __builtin_nontemporal_load(&src[i * stride_words]);
 }
 
-// A run's last kernel where it has none of its own.
-__global__ void k_finish(const uint32_t* err, uint32_t* h_err) {
+// A run's last kernel where it has none of its own: one workgroup of kSumSlots lanes reports
+// the watchdog word and, where there are partial sums, adds them to the output.
+__global__ void k_finish(const uint32_t* err, uint32_t* h_err, const unsigned long long* sums,
+                         unsigned long long* out) {
+  __shared__ unsigned long long w[spi::kSumSlots / 64];
   if (threadIdx.x == 0) spi::report_error(err, h_err);
+  if (!sums) return;
+  unsigned long long v = sums[threadIdx.x * spi::kSumStride];
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (uint32_t i = 1; i < spi::kSumSlots / 64; ++i) v += w[i];
+  *out += v;
 }
 
 __global__ void k_probe_xcc(uint32_t* out) {
@@ -83,7 +94,6 @@ int fill_u32(sp_ctx* ctx, uint32_t* d, uint64_t words, uint32_t value, hipStream
 }
 
 int resident_per_cu(sp_ctx* ctx, const void* kern, uint32_t lanes, uint32_t* per_cu) {
-  std::lock_guard<std::mutex> hold(ctx->occupancy_mu);
   for (const auto& o : ctx->occupancy)
     if (o.kern == kern && o.lanes == lanes) {
       *per_cu = o.per_cu;
@@ -108,10 +118,11 @@ bool capturing(hipStream_t s) {
   return s && hipStreamIsCapturing(s, &c) == hipSuccess && c == hipStreamCaptureStatusActive;
 }
 
-int sync_unless_capturing(sp_ctx* ctx, hipStream_t s) {
-  if (capturing(s)) return SP_OK;
-  SP_HIP(ctx, hipStreamSynchronize(s));
-  return SP_OK;
+Sums sums_for(sp_ctx* ctx, unsigned long long* out, hipStream_t s, Resets* z) {
+  z->add(out, 2);
+  if (capturing(s)) return Sums{out, 0};
+  z->add(ctx->d_sums, 2ull * kSumSlots * kSumStride);
+  return Sums{ctx->d_sums, kSumSlots - 1};
 }
 
 int begin_timed(sp_ctx* ctx, hipStream_t s, Resets z) {
@@ -154,7 +165,13 @@ int wait_done(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t l
 int end_timed(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
               uint32_t resident_per_cu, uint64_t ops) {
   SP_CHECK(mark_end(ctx, s));
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, s, ctx->d_err, ctx->h_err);
+  return finish(ctx, s, st, nwg, lanes, resident_per_cu, ops, Sums{nullptr, 0}, nullptr);
+}
+
+int finish(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
+           uint32_t resident_per_cu, uint64_t ops, const Sums& sums, unsigned long long* out) {
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(kSumSlots), 0, s, ctx->d_err, ctx->h_err,
+                     sums.mask ? sums.p : nullptr, out);
   return wait_done(ctx, s, st, nwg, lanes, resident_per_cu, ops);
 }
 
@@ -230,6 +247,9 @@ int sp_init(int device, sp_ctx** out) {
     ctx->wall_khz = (uint32_t)khz;
   if ((e = hipMalloc(&ctx->d_err, 256)) != hipSuccess) return fail(e);
   if ((e = hipMalloc(&ctx->d_scratch, 4096)) != hipSuccess) return fail(e);
+  if ((e = hipMalloc(&ctx->d_sums, sizeof(unsigned long long) * spi::kSumSlots *
+                                       spi::kSumStride)) != hipSuccess)
+    return fail(e);
   if ((e = hipHostMalloc((void**)&ctx->h_err, 4096,
                          hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess)
     return fail(e);
@@ -311,6 +331,7 @@ int sp_fini(sp_ctx* ctx) {
   (void)hipStreamDestroy(ctx->capture_stream);
   (void)hipEventDestroy(ctx->ev1);
   (void)hipEventDestroy(ctx->ev0);
+  (void)hipFree(ctx->d_sums);
   (void)hipHostFree(ctx->h_stage);
   (void)hipHostFree(ctx->h_err);
   (void)hipFree(ctx->d_scratch);
@@ -318,6 +339,7 @@ int sp_fini(sp_ctx* ctx) {
   ctx->capture_stream = ctx->setup_stream = nullptr;
   ctx->ev0 = ctx->ev1 = nullptr;
   ctx->d_err = ctx->d_scratch = ctx->h_err = ctx->h_stage = nullptr;
+  ctx->d_sums = nullptr;
   ctx->closed = true;
   if (ctx->refs == 0) delete ctx;
   return SP_OK;
@@ -405,7 +427,6 @@ int sp_buffer_read_strided(sp_ctx* ctx, uint32_t* host_dst, const uint32_t* dev_
   hipStream_t s = spi::as_stream(stream);
   if (spi::capturing(s)) return SP_E_INVAL;
   SP_HIP(ctx, hipSetDevice(ctx->device));
-  std::lock_guard<std::mutex> hold(ctx->stage_mu);
   if (!ctx->h_stage)
     SP_HIP(ctx, hipHostMalloc((void**)&ctx->h_stage, kStageWords * sizeof(uint32_t),
                               hipHostMallocMapped));

@@ -8,8 +8,8 @@
 
 namespace {
 
-// Block-wide sum of a per-thread uint64 followed by one atomic per workgroup.
-__device__ void block_sum_to(unsigned long long v, unsigned long long* out) {
+// Block-wide sum of a per-thread uint64 followed by one atomic per workgroup, on its slot.
+__device__ void block_sum_to(unsigned long long v, const spi::Sums& out) {
   __shared__ unsigned long long part[16];
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -18,7 +18,7 @@ __device__ void block_sum_to(unsigned long long v, unsigned long long* out) {
   if (threadIdx.x == 0) {
     unsigned long long s = 0;
     for (uint32_t w = 0; w < (blockDim.x + 63) / 64; ++w) s += part[w];
-    atomicAdd(out, s);
+    atomicAdd(out.slot(blockIdx.x), s);
   }
 }
 
@@ -34,7 +34,7 @@ __global__ void k_prefill(uint32_t* buf, uint32_t T, uint32_t stride_words, uint
 template <int OP, int MODE>
 __global__ SP_FULL_OCCUPANCY void k_bench_atomic(uint32_t T, uint32_t stride_words, uint64_t n, uint32_t seed,
                                const uint32_t* __restrict__ perm, uint32_t* buf,
-                               unsigned long long* out_sum, uint32_t* err, uint64_t timeout) {
+                               spi::Sums out_sum, uint32_t* err, uint64_t timeout) {
   const sp::Ctl ctl{err, sp::wall_clock() + timeout};
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t waves = blockDim.x >> 6;
@@ -77,7 +77,7 @@ __global__ SP_FULL_OCCUPANCY void k_bench_atomic(uint32_t T, uint32_t stride_wor
 
 // Adds the final word values (for the exchange conservation sum).
 __global__ void k_sum_words(const uint32_t* buf, uint32_t T, uint32_t stride_words,
-                            unsigned long long* out_sum) {
+                            spi::Sums out_sum) {
   unsigned long long s = 0;
   for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < T; t += gridDim.x * blockDim.x)
     s += buf[(size_t)t * stride_words];
@@ -122,22 +122,34 @@ __global__ void k_paper12(uint32_t test, uint32_t n, uint32_t stride_words, uint
   atomicAdd(out_sum, s);
 }
 
-// Streaming read: 16-byte loads, grid-stride, uint32 words summed.
-// Four independent 16-byte loads per lane in flight per step (each one coalesced across
-// the wavefront), then the grid-stride tail one at a time; the sum is exact in any order.
-__global__ void k_stream(const uint4* __restrict__ buf, uint64_t n16, uint32_t reps,
-                         unsigned long long* out_sum) {
+// Streaming read, uint32 words summed (exact in any order).  HBM bounds it.  Every workgroup
+// reads one contiguous piece, eight independent 16-byte loads per lane in flight, each load
+// 1 KiB per wavefront; NT: loads that the caches do not keep, for a buffer read once.
+// 1 GiB on an MI355X (kernel alone): grid-stride with four loads 197 us (5.4 TB/s), pieces
+// with four or eight loads 177 us (6.1), pieces with eight nontemporal loads 154 us (7.0);
+// sixteen 157, eight grid-stride nontemporal loads 172.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <bool NT>
+__global__ void k_stream(const u32x4* __restrict__ buf, uint64_t n16, uint32_t reps,
+                         spi::Sums out_sum) {
+  constexpr uint32_t kLoads = 8;
   unsigned long long s = 0;
-  const uint64_t g = (uint64_t)gridDim.x * blockDim.x;
+  // whole wavefront loads per piece; the last pieces of a small buffer are empty
+  const uint64_t piece = ((n16 + gridDim.x - 1) / gridDim.x + 63) / 64 * 64;
+  const uint64_t begin = std::min(piece * blockIdx.x, n16), end = std::min(begin + piece, n16);
   for (uint32_t r = 0; r < reps; ++r) {
-    uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    for (; i + 3 * g < n16; i += 4 * g) {
-      const uint4 a = buf[i], b = buf[i + g], c = buf[i + 2 * g], d = buf[i + 3 * g];
-      s += (unsigned long long)a.x + a.y + a.z + a.w + b.x + b.y + b.z + b.w;
-      s += (unsigned long long)c.x + c.y + c.z + c.w + d.x + d.y + d.z + d.w;
+    uint64_t i = begin + threadIdx.x;
+    for (; i + (kLoads - 1) * blockDim.x < end; i += kLoads * blockDim.x) {
+      u32x4 v[kLoads];
+#pragma unroll
+      for (uint32_t u = 0; u < kLoads; ++u)
+        v[u] = NT ? __builtin_nontemporal_load(&buf[i + u * blockDim.x]) : buf[i + u * blockDim.x];
+#pragma unroll
+      for (uint32_t u = 0; u < kLoads; ++u)
+        s += (unsigned long long)v[u].x + v[u].y + v[u].z + v[u].w;
     }
-    for (; i < n16; i += g) {
-      const uint4 v = buf[i];
+    for (; i < end; i += blockDim.x) {
+      const u32x4 v = NT ? __builtin_nontemporal_load(&buf[i]) : buf[i];
       s += (unsigned long long)v.x + v.y + v.z + v.w;
     }
   }
@@ -268,13 +280,14 @@ int sp_bench_atomic(sp_ctx* ctx, uint32_t op, uint32_t nwg, uint32_t lanes, uint
   const uint32_t hashed = op == SP_OP_EXCH || op == SP_OP_LD;
   hipLaunchKernelGGL(k_prefill, dim3(std::min<uint32_t>((T + 255) / 256, 4096)), dim3(256), 0, s,
                      buf, T, sw, seed, hashed);
-  SP_CHECK(spi::fill_u32(ctx, reinterpret_cast<uint32_t*>(out_sum), 2, 0, s));
   const void* kern = bench_kernel(op, mode);
   uint32_t per_cu = 0;
   SP_CHECK(spi::resident_per_cu(ctx, kern, lanes, &per_cu));
-  SP_CHECK(spi::begin_timed(ctx, s));
+  spi::Resets z;
+  unsigned long long* out = reinterpret_cast<unsigned long long*>(out_sum);
+  spi::Sums sum = spi::sums_for(ctx, out, s, &z);
+  SP_CHECK(spi::begin_timed(ctx, s, z));
   uint64_t n = ops_per_issuer;
-  unsigned long long* sum = reinterpret_cast<unsigned long long*>(out_sum);
   sp_params q;
   sp_params_default(&q);
   uint64_t timeout = spi::timeout_ticks(ctx, q);
@@ -282,14 +295,11 @@ int sp_bench_atomic(sp_ctx* ctx, uint32_t op, uint32_t nwg, uint32_t lanes, uint
   SP_HIP(ctx, hipLaunchKernel(kern, dim3(nwg), dim3(lanes), args, 0, s));
   const uint64_t issuers =
       mode == SP_ISSUE_PER_LANE ? (uint64_t)nwg * lanes : (uint64_t)nwg * (lanes / 64);
-  SP_CHECK(spi::end_timed(ctx, s, st, nwg, lanes, (uint32_t)per_cu, issuers * n));
-  if (op == SP_OP_EXCH) {
+  SP_CHECK(spi::mark_end(ctx, s));
+  if (op == SP_OP_EXCH)
     hipLaunchKernelGGL(k_sum_words, dim3(std::min<uint32_t>((T + 255) / 256, 4096)), dim3(256), 0,
                        s, buf, T, sw, sum);
-    SP_HIP(ctx, hipGetLastError());
-    SP_CHECK(spi::sync_unless_capturing(ctx, s));
-  }
-  return SP_OK;
+  return spi::finish(ctx, s, st, nwg, lanes, (uint32_t)per_cu, issuers * n, sum, out);
 }
 
 int sp_bench_paper12(sp_ctx* ctx, uint32_t test, uint32_t nwg, uint32_t lanes, uint32_t n_ops,
@@ -316,14 +326,20 @@ int sp_bench_stream(sp_ctx* ctx, const void* buf, uint64_t bytes, uint32_t nwg, 
   if (!spi::usable(ctx) || !buf || !out_sum || bytes == 0 || bytes % 16 || reps == 0) return SP_E_INVAL;
   hipStream_t s = spi::as_stream(stream);
   SP_HIP(ctx, hipSetDevice(ctx->device));
-  // 32 per CU: with four loads in flight per lane, 8192 workgroups read 1 GiB at 7.1-7.3
-  // TB/s on an MI355X against 5.4 with 8 per CU (and 6.6 for one load per lane at best)
+  // 32 per CU: 1 GiB takes 154-157 us with 4, 8, 16, 32 or 64
   if (nwg == 0) nwg = ctx->cu_count * 32;
-  SP_CHECK(spi::fill_u32(ctx, reinterpret_cast<uint32_t*>(out_sum), 2, 0, s));
-  SP_CHECK(spi::begin_timed(ctx, s));
-  hipLaunchKernelGGL(k_stream, dim3(nwg), dim3(256), 0, s, (const uint4*)buf, bytes / 16, reps,
-                     reinterpret_cast<unsigned long long*>(out_sum));
-  return spi::end_timed(ctx, s, st, nwg, 256, 0, bytes * reps);
+  spi::Resets z;
+  unsigned long long* out = reinterpret_cast<unsigned long long*>(out_sum);
+  const spi::Sums sum = spi::sums_for(ctx, out, s, &z);
+  SP_CHECK(spi::begin_timed(ctx, s, z));
+  // Nontemporal loads, except for a buffer that several passes find in the 256 MiB memory-side
+  // cache after ordinary ones.  Ten passes, ordinary against nontemporal: 64 MiB 36 and 63 us,
+  // 256 MiB 109 and 298, 1 GiB 1581 and 1444.
+  const bool nt = reps == 1 || bytes > (256ull << 20);
+  hipLaunchKernelGGL(nt ? k_stream<true> : k_stream<false>, dim3(nwg), dim3(256), 0, s,
+                     (const u32x4*)buf, bytes / 16, reps, sum);
+  SP_CHECK(spi::mark_end(ctx, s));
+  return spi::finish(ctx, s, st, nwg, 256, 0, bytes * reps, sum, out);
 }
 
 int sp_bench_clock(sp_ctx* ctx, uint32_t ms, uint64_t* out, double* mhz, void* stream) {

@@ -5,7 +5,6 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <mutex>
 #include <vector>
 
 #include "sp.h"
@@ -35,11 +34,10 @@ struct sp_ctx {
   uint32_t* h_err = nullptr;   // pinned: the watchdog word as a run's last kernel found it
   // pinned staging of sp_buffer_read_strided, made by its first call
   uint32_t* h_stage = nullptr;
-  std::mutex stage_mu;
+  unsigned long long* d_sums = nullptr;  // kSumSlots partial sums, one per 128-byte line
   // occupancy of the library's kernels, asked of the runtime once per kernel and size
   struct Occupancy { const void* kern; uint32_t lanes, per_cu; };
   std::vector<Occupancy> occupancy;
-  std::mutex occupancy_mu;
   uint32_t* d_scratch = nullptr;  // small staging area (4 KiB) for state readback
   // the allocation-free entry point's fixed workspace on this device (a file-scope device
   // array; its address is looked up once per device at sp_init)
@@ -126,8 +124,6 @@ int fill_u32(sp_ctx* ctx, uint32_t* d, uint64_t words, uint32_t value, hipStream
 // True while `s` is being captured into a HIP graph (sp_graph_begin): run calls then
 // record their kernels and skip timing, host waits and host readbacks.
 bool capturing(hipStream_t s);
-// hipStreamSynchronize(s), or nothing while `s` is being captured.
-int sync_unless_capturing(sp_ctx* ctx, hipStream_t s);
 
 // Around a run's main kernel.  begin_timed resets `z` and the watchdog word and records
 // ev0; mark_end records ev1; the run's last kernel (its own, or end_timed's) copies the
@@ -142,13 +138,31 @@ int begin_timed(sp_ctx* ctx, hipStream_t s, Resets z = Resets());
 int mark_end(sp_ctx* ctx, hipStream_t s);
 int wait_done(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
               uint32_t resident_per_cu, uint64_t ops);
-// mark_end, a one-lane kernel that reports the watchdog word, wait_done.
 int end_timed(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
               uint32_t resident_per_cu, uint64_t ops);
 __device__ __forceinline__ void report_error(const uint32_t* err, uint32_t* h_err) {
   __hip_atomic_store(h_err, __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+// Where the workgroups of a microbenchmark add their sums.  One word takes atomics 12 ns
+// apart, so the sums of 8192 workgroups took 104 us behind a 64 MiB read of 14 us: workgroup
+// b adds to slot b mod kSumSlots, each on its own line, and the call's last kernel adds the
+// slots to the output.  The slots are the context's, so a recorded call, which may be
+// replayed beside others, adds to the output itself (mask 0).
+constexpr uint32_t kSumSlots = 256, kSumStride = 16;
+struct Sums {
+  unsigned long long* p;
+  uint32_t mask;
+  __device__ unsigned long long* slot(uint32_t b) const { return p + (b & mask) * kSumStride; }
+};
+// The sums of a call on `s`; what they need reset is added to z.
+Sums sums_for(sp_ctx* ctx, unsigned long long* out, hipStream_t s, Resets* z);
+
+// A kernel that reports the watchdog word and adds the slots (if any) to `out`, then
+// wait_done.  end_timed: mark_end, then this without sums.
+int finish(sp_ctx* ctx, hipStream_t s, sp_stats* st, uint32_t nwg, uint32_t lanes,
+           uint32_t resident_per_cu, uint64_t ops, const Sums& sums, unsigned long long* out);
+
 // Workgroups of `kern` (launched with `lanes` threads) that fit on one CU at once: the
 // runtime's occupancy figure checked against the kernel's own VGPR and LDS use
 // (sp_resident_per_cu).

@@ -173,3 +173,45 @@ def test_finals_of_strided_words(ctx, T, stride):
         pos = (np.arange(16 * 64)[:, None] + np.arange(3)[None, :]) % T
         want = np.bincount(perm[pos].ravel(), minlength=T).astype(np.uint32)
         assert finals.dtype == np.uint32 and (finals == want).all()
+
+
+@pytest.mark.parametrize("reps", [1, 3])
+@pytest.mark.parametrize("n16,nwg", [
+    (1, 0), (63, 1), (64, 1), (65, 2), (2047, 1), (2049, 1), (16 * 2048 + 5, 3),
+    (8192 * 64 - 1, 0), (8192 * 64 + 1, 0), (1_000_003, 777), (5 << 20, 0),
+])
+def test_stream_sums_at_piece_edges(ctx, n16, nwg, reps):
+    """Pieces of whole wavefront loads, empty last pieces, loads left over from a step of
+    eight, more workgroups than sum slots; the sum is exact."""
+    import numpy as np
+
+    import paper_1110_4623_amd as sp
+    announce("stream", n16, nwg, reps)
+    words = np.random.default_rng(n16).integers(0, 1 << 32, 4 * n16, dtype=np.uint64)
+    words = words.astype(np.uint32)
+    buf = ctx.upload(words)
+    s, st = sp.stream_read(ctx, buf, 16 * n16, reps=reps, nwg=nwg)
+    assert s == reps * int(words.sum(dtype=np.uint64)) and st["device_error"] == 0
+
+
+def test_stream_sum_in_a_graph(ctx):
+    """A recorded read adds to its own output: replays beside eager reads of the same
+    context keep both sums."""
+    import ctypes
+
+    import numpy as np
+
+    import paper_1110_4623_amd as sp
+    from paper_1110_4623_amd import _native as N
+    announce("stream in a graph")
+    a, b = (ctx.upload(np.full(1 << 20, v, np.uint32)) for v in (3, 5))
+    out, st = ctx.zeros(1, "u64"), N.Stats()
+    g = sp.Graph(ctx)
+    with g:
+        assert N.lib.sp_bench_stream(ctx.h, ctx.ptr(a), 4 << 20, 0, 2, ctx.ptr(out),
+                                     ctypes.byref(st), ctx.stream()) == 0
+    for _ in range(3):
+        g.launch()
+        assert sp.stream_read(ctx, b, 4 << 20)[0] == 5 << 20
+        assert int(ctx.read(out, "u64", 1)[0]) == 2 * 3 << 20
+    g.close()
