@@ -31,12 +31,11 @@ template <int MKIND, bool FENCED = true>
 __device__ bool cond_wait(const CondState& cv, const MutexState& m, uint32_t lock,
                           MutexHold* hold, const Ctl& ctl) {
   __shared__ uint32_t s_ok;
-  __shared__ uint32_t s_ticket;
-  if (is_leader()) s_ticket = add_relaxed(cv.waiters, 1);
+  uint32_t t = 0;
+  if (is_leader()) t = add_relaxed(cv.waiters, 1);
   mutex_unlock<MKIND, FENCED>(m, lock, hold);
   if (is_leader()) {
     Wait w(ctl, cv.poll_sleep);
-    const uint32_t t = s_ticket;
     s_ok = poll(w, [&] { return (int32_t)uniform(ld_relaxed(cv.signals) - t) > 0; });
   }
   __syncthreads();
@@ -54,6 +53,29 @@ __device__ __forceinline__ void cond_signal_leader(const CondState& cv) {
     if (seen == s) return;
     s = seen;
   }
+}
+
+// A signal in three steps, for a leader that holds the mutex and has other round trips to
+// make: cond_peek loads the counters beside the protected data, cond_signal_begin releases
+// the next ticket if one waits, and cond_signal_end, best after the unlock, looks at what
+// that found (a signaller that does not hold the mutex came between: then once more, which
+// without the mutex is a signal too, only a later one).
+struct CondPeek {
+  uint32_t signals, waiters;
+};
+__device__ __forceinline__ CondPeek cond_peek(const CondState& cv) {
+  CondPeek k;
+  k.signals = ld_relaxed(cv.signals);
+  k.waiters = ld_relaxed(cv.waiters);
+  return k;
+}
+__device__ __forceinline__ uint32_t cond_signal_begin(const CondState& cv, const CondPeek& k) {
+  if ((int32_t)(k.waiters - k.signals) <= 0) return k.signals;
+  return cas_relaxed(cv.signals, k.signals, k.signals + 1);
+}
+__device__ __forceinline__ void cond_signal_end(const CondState& cv, const CondPeek& k,
+                                                uint32_t seen) {
+  if (seen != k.signals) cond_signal_leader(cv);
 }
 
 __device__ __forceinline__ void cond_broadcast_leader(const CondState& cv) {
