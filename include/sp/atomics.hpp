@@ -157,6 +157,14 @@ __device__ __forceinline__ void fence_release() {
   wave_stores_complete();
 }
 
+// Every wavefront's stores complete before the workgroup barrier that precedes a leader's
+// fence_release(); without that fence (`fenced` false) the leader's too.  The leader's own
+// wavefront need not wait with it: the fence writes back what the wavefront stored before it
+// and waits for both (the wait cost ~150 shader clocks of every hand-over).
+__device__ __forceinline__ void stores_complete_before_release(bool fenced) {
+  if (!fenced || __builtin_amdgcn_readfirstlane(threadIdx.x) >= 64) wave_stores_complete();
+}
+
 // A workgroup-scope invalidate (buffer_inv sc0).  It costs ~310 shader clocks and is not
 // serialized at the L2, unlike the agent-scope one; but it does not make another XCD's
 // written-back data visible: after it, a plain load returned the old value in 28 % of

@@ -428,7 +428,8 @@ template <int KIND>
 __device__ bool barrier_wait(const BarrierState& s, uint32_t round, const Ctl& ctl) {
   __shared__ uint32_t s_ok;
   const uint32_t stamp = round + 1;
-  wave_stores_complete();
+  // (the per-XCD barrier's workgroups arrive without a release fence)
+  stores_complete_before_release(KIND != SP_BARRIER_XCD && s.fenced);
   if constexpr (KIND == SP_BARRIER_FLAG) {
     return detail::flag_wait(s, stamp, ctl);
   } else if constexpr (KIND == SP_BARRIER_XCD) {

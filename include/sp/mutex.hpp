@@ -379,7 +379,7 @@ template <int KIND, bool FENCED = true>
 __device__ void mutex_unlock(const MutexState& s, uint32_t lock, const MutexHold* hold = nullptr,
                              const Ctl* ctl = nullptr) {
   if constexpr (KIND == SP_MUTEX_MCS) {
-    wave_stores_complete();
+    stores_complete_before_release(FENCED);
     __syncthreads();
     if (!is_leader()) return;
     uint32_t* node = mcs_node(s, lock, blockIdx.x);
@@ -456,7 +456,7 @@ __device__ void mutex_unlock(const MutexState& s, uint32_t lock, const MutexHold
     st_cu(line, pass ? grant : grant & kTurnMask);
     return;
   }
-  wave_stores_complete();
+  stores_complete_before_release(FENCED);
   __syncthreads();
   if (is_leader()) {
     uint32_t* w;

@@ -387,7 +387,8 @@ __device__ bool sem_post(const SemState& s, const Ctl& ctl, const SemHold* hold 
     return true;
   }
   __shared__ uint32_t s_ok;
-  wave_stores_complete();
+  // these two hand units on within an XCD without a release fence
+  stores_complete_before_release(FENCED && KIND != SP_SEM_COHORT && KIND != SP_SEM_XCD_CHAIN);
   __syncthreads();
   if constexpr (KIND == SP_SEM_COHORT) {
     // Hand the unit on.  Algorithm 5's post: write back, then decrement count; if a waiter
