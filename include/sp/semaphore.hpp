@@ -379,8 +379,9 @@ __device__ bool sem_wait(const SemState& s, const Ctl& ctl, SemHold* hold = null
 
 // `hold`: SP_SEM_COHORT needs the record its sem_wait filled in (the unit's local
 // hand-overs), SP_SEM_CHAIN and SP_SEM_XCD_CHAIN require it (the ticket and queue, so not
-// null); other kinds ignore it.
-template <int KIND, bool FENCED = true>
+// null); other kinds ignore it.  COMPLETE = false: no wait for the workgroup's stores first
+// (the caller has waited for those that a next holder must see).
+template <int KIND, bool FENCED = true, bool COMPLETE = true>
 __device__ bool sem_post(const SemState& s, const Ctl& ctl, const SemHold* hold = nullptr) {
   if constexpr (KIND == SP_SEM_CU_LOCK) {
     mutex_unlock<SP_MUTEX_CU_COHORT, FENCED>(cu_lock_state(s), 0, &hold->lock, &ctl);
@@ -388,7 +389,8 @@ __device__ bool sem_post(const SemState& s, const Ctl& ctl, const SemHold* hold 
   }
   __shared__ uint32_t s_ok;
   // these two hand units on within an XCD without a release fence
-  stores_complete_before_release(FENCED && KIND != SP_SEM_COHORT && KIND != SP_SEM_XCD_CHAIN);
+  if constexpr (COMPLETE)
+    stores_complete_before_release(FENCED && KIND != SP_SEM_COHORT && KIND != SP_SEM_XCD_CHAIN);
   __syncthreads();
   if constexpr (KIND == SP_SEM_COHORT) {
     // Hand the unit on.  Algorithm 5's post: write back, then decrement count; if a waiter

@@ -51,6 +51,10 @@ constexpr uint32_t kCohortSlots = 4096;
 // tracker's words instead of three and waits for one instead of two.
 // 2048 workgroups, K = 32, 2^18 tracked pairs: 16.4 ms against 17.1; 257 workgroups, K = 4,
 // 2^14 pairs with the pool: 11.8 ms against 12.8.
+// The slot's return is on its way when the unit is posted: a next holder that comes before it
+// finds the slot taken and looks on (257 workgroups, K = 4: 9.8 ms against 11.1).  Loading
+// the owners of several slots beside the first compare-and-swap was slower than trying one
+// after the other (K = 4: 10.8 ms; 300 workgroups, K = 32: 7.2 against 5.9).
 template <int KIND, bool FENCED>
 __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_t* state, uint32_t nwg,
                       uint64_t total, uint32_t max_hold, uint32_t seed, uint32_t track,
@@ -85,7 +89,7 @@ __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_
         // at most K holders, so some slot is free; start where the schedule says
         sp::Wait w(ctl, 0);
         slot = first;
-        while (sp::cas_relaxed(owner + (size_t)slot * kOwnerWords, 0, b + 1) != 0) {
+        while (sp::uniform(sp::cas_relaxed(owner + (size_t)slot * kOwnerWords, 0, b + 1)) != 0) {
           slot = slot + 1 == s.K ? 0 : slot + 1;
           if (!w.tick()) {
             slot = s.K;
@@ -111,14 +115,16 @@ __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_
       }
     }
     if (pool) {
-      sp::wave_stores_complete();
+      sp::stores_complete_before_release(FENCED);
       __syncthreads();
       if (sp::is_leader()) {
         if constexpr (FENCED) sp::st_release(owner + (size_t)slot * kOwnerWords, 0);
         else sp::st_relaxed(owner + (size_t)slot * kOwnerWords, 0);
       }
     }
-    if (!(pool ? sp::sem_post<KIND, false>(s, ctl, &sh) : sp::sem_post<KIND, FENCED>(s, ctl, &sh)))
+    // (the next holder may come before the slot's return lands: it then finds it taken)
+    if (!(pool ? sp::sem_post<KIND, false, false>(s, ctl, &sh)
+               : sp::sem_post<KIND, FENCED>(s, ctl, &sh)))
       break;
   }
   if (sp::is_leader()) {

@@ -215,3 +215,23 @@ def test_stream_sum_in_a_graph(ctx):
         assert sp.stream_read(ctx, b, 4 << 20)[0] == 5 << 20
         assert int(ctx.read(out, "u64", 1)[0]) == 2 * 3 << 20
     g.close()
+
+
+@pytest.mark.parametrize("coherent", [0, 1])
+@pytest.mark.parametrize("kind", ["sleep", "array", "chain", "xcd_chain", "cohort"])
+@pytest.mark.parametrize("K,nwg,lanes", [(2, 2, 64), (2, 64, 256), (3, 3, 128), (4, 257, 64),
+                                         (64, 65, 192)])
+def test_pool_slots_returned_behind_the_post(ctx, kind, K, nwg, lanes, coherent):
+    """A holder admitted before its predecessor's slot is back: every update of the pool's
+    words is kept, with as many holders as slots and with one more."""
+    import paper_1110_4623_amd as sp
+    if kind == "xcd_chain" and K < ctx.info["xcd_count"]:
+        pytest.skip("a unit per XCD at least")
+    announce("pool", kind, K, nwg, lanes, coherent)
+    s = sp.Semaphore(ctx, kind, K, coherent_cs=coherent)
+    try:
+        r = s.run(nwg, lanes, 5000, 0, 11, track=True, data=True)
+    finally:
+        s.close()
+    assert (r["chk"] == oracle.sem_closed(11, nwg, 5000)).all()
+    assert 1 <= r["maxocc"] <= K and int(r["data"].astype("u8").sum()) == 5000
