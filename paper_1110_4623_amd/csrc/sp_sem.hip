@@ -79,10 +79,7 @@ __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_
     if (!(pool ? sp::sem_wait<KIND, false>(s, ctl, &sh) : sp::sem_wait<KIND, FENCED>(s, ctl, &sh)))
       break;
     uint32_t inside = 0;
-    if (sp::is_leader()) {
-      if (track) inside = sp::add_relaxed(occ, 1) + 1;
-      c ^= sp::sm32(seed ^ (b << 16) ^ (uint32_t)j);
-    }
+    if (track && sp::is_leader()) inside = sp::add_relaxed(occ, 1) + 1;
     uint32_t slot = 0;
     if (pool) {
       if (sp::is_leader()) {
@@ -109,10 +106,7 @@ __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_
     }
     if (sp::is_leader()) {
       sp::spin_cycles(hold);
-      if (track) {
-        most = inside > most ? inside : most;
-        sp::add_relaxed(occ, 0xFFFFFFFFu);
-      }
+      if (track) sp::add_relaxed(occ, 0xFFFFFFFFu);
     }
     if (pool) {
       sp::stores_complete_before_release(FENCED);
@@ -126,6 +120,8 @@ __global__ SP_FULL_OCCUPANCY void k_sem(sp::SemState s, uint32_t stride, uint32_
     if (!(pool ? sp::sem_post<KIND, false, false>(s, ctl, &sh)
                : sp::sem_post<KIND, FENCED>(s, ctl, &sh)))
       break;
+    most = inside > most ? inside : most;  // (after the post: nobody waits for the add's value)
+    c ^= sp::sm32(seed ^ (b << 16) ^ (uint32_t)j);
   }
   if (sp::is_leader()) {
     if (most) sp::max_relaxed(maxocc, most);
