@@ -15,7 +15,7 @@ struct sp_barrier {
   sp_params p{};
   uint32_t* d_state = nullptr;  // counters and flags
   uint64_t state_words = 0;
-  uint32_t* d_slots = nullptr;  // 2 x nwg exchanged values
+  uint32_t* d_slots = nullptr;  // exchanged values of two rounds (slot_layout)
   uint32_t* d_near = nullptr;   // per-XCD blocks in measured chunks (flag_placement 0)
   uint64_t near_words = 0;
   uint32_t near_placed = 0;     // bits: 1 arrival blocks, 2 stamp copies, 4 release lines
@@ -25,6 +25,33 @@ struct sp_barrier {
 
 namespace {
 
+// Where the exchanged values of one round lie: workgroup w's at block w mod blocks, place
+// w / blocks of it, `step` words apart, blocks of whole lines.
+struct SlotLayout {
+  uint32_t blocks, block_words, step;
+  __host__ __device__ uint32_t half() const { return blocks * block_words; }
+  __host__ __device__ uint32_t word(uint32_t w) const {
+    return w % blocks * block_words + w / blocks * step;
+  }
+};
+
+// A packed array of all values had every XCD write and read every line.  Plain values: a
+// block per XCD (workgroups are dealt to the XCDs in turn), packed, so that a line is written
+// back by one XCD, whole, and one XCD's readers of a round want one block.  Agent-scope
+// values: a line each, since accesses to one line take their turns (32 workgroups' stores
+// and 32 loads of them took most of a 1.1 us exchange).
+// Per round, packed array -> this: 16 workgroups, central barrier, 1.75 -> 1.72 us, agent-scope
+// values 1.86 -> 1.38; 1024 of 256 lanes 4.76 -> 4.43, 2.89 -> 2.24; 2048 of 256 lanes
+// 5.13 -> 4.81, 3.22 -> 2.68.
+SlotLayout slot_layout(uint32_t nwg, uint32_t xcds, bool coherent) {
+  const uint32_t most = 1u << 16;  // (more workgroups than can run: no room for lines)
+  SlotLayout at;
+  at.blocks = std::max<uint32_t>(1, xcds);
+  at.step = coherent && nwg <= most ? 32 : 1;
+  at.block_words = ((nwg + at.blocks - 1) / at.blocks * at.step + 31) / 32 * 32;
+  return at;
+}
+
 // Hash-exchange workload: the slot is written by the workgroup's last thread and read
 // by thread 64 (a different wavefront when the workgroup has more than one), with plain
 // stores and loads, so only the barrier orders them -- or, for a barrier created with
@@ -32,34 +59,51 @@ namespace {
 // the barrier then orders without cache maintenance.
 template <int KIND, bool COHERENT>
 __global__ SP_FULL_OCCUPANCY void k_barrier_hash(sp::BarrierState s, uint32_t rounds, uint32_t seed,
-                               uint32_t* slots, uint32_t* out, uint32_t* err,
+                               uint32_t* slots, SlotLayout at, uint32_t* out, uint32_t* err,
                                uint64_t timeout) {
   const sp::Ctl ctl{err, sp::wall_clock() + timeout};
   const uint32_t b = blockIdx.x, N = s.nwg;
   const uint32_t writer = blockDim.x - 1, reader = 64 % blockDim.x;
-  uint32_t chk = 0;
+  uint32_t chk = 0, got = 0;
   // What a round stores and where it reads are found before its barrier, so that after it
   // only the load and the next store stand on the way to the next one (a 64-bit remainder
   // and a hash there cost 0.1-0.2 us: 2048 workgroups 5.18 us per round from 5.27, 1000 of
   // 192 lanes, coherent data, 2.81 from 3.06).
-  uint32_t v = sp::sm32(seed ^ (b << 16)), from = b;
+  uint32_t v = sp::sm32(seed ^ (b << 16));
+  // the writer's place, and the reader's, which walks the layout one workgroup a round; in
+  // vector registers, which are plenty (the per-XCD barrier takes all the scalar ones)
+  uint32_t mine = at.word(b), word = at.word(b), left = N - b, block = b % at.blocks;
+  uint32_t blocks = at.blocks, next_block = at.block_words;
+  uint32_t next_place = at.step - at.blocks * at.block_words;  // from the block after the last
+  __asm__("" : "+v"(mine), "+v"(word), "+v"(left), "+v"(block));
+  __asm__("" : "+v"(blocks), "+v"(next_block), "+v"(next_place));
   for (uint32_t r = 0; r < rounds; ++r) {
-    uint32_t* half = slots + (r & 1) * N;
+    uint32_t* half = slots + (r & 1) * at.half();
     if (threadIdx.x == writer) {
-      if constexpr (COHERENT) sp::st_relaxed(half + b, v);
-      else half[b] = v;
+      if constexpr (COHERENT) sp::st_relaxed(half + mine, v);
+      else half[mine] = v;
     }
-    const uint32_t* src = half + from;
-    __asm__ __volatile__("" : "+s"(src));
-    from = from + 1 == N ? 0 : from + 1;  // (b + r + 1) mod N
+    const uint32_t* src = half + word;
+    if (threadIdx.x == reader) {  // on to (b + r + 1) mod N
+      word += next_block;
+      if (++block == blocks) {
+        block = 0;
+        word += next_place;
+      }
+      if (--left == 0) {
+        word = block = 0;
+        left = N;
+      }
+    }
     v = sp::computed_here(sp::sm32(seed ^ (b << 16) ^ (r + 1)));
+    chk ^= got;  // (the last round's load, waited for behind this round's store)
     if (!sp::barrier_wait<KIND>(s, r, ctl)) return;
     if (threadIdx.x == reader) {
-      if constexpr (COHERENT) chk ^= sp::ld_relaxed(src);
-      else chk ^= *src;
+      if constexpr (COHERENT) got = sp::ld_relaxed(src);
+      else got = *src;
     }
   }
-  if (threadIdx.x == reader) out[b] = chk;
+  if (threadIdx.x == reader) out[b] = chk ^ got;
 }
 
 // Comparator: HIP cooperative groups' grid-wide barrier.
@@ -259,10 +303,11 @@ int sp_barrier_create(sp_ctx* ctx, uint32_t kind, uint32_t nwg, const sp_params*
   const uint64_t lines =
       5 + 3ull * G + 2 * flag_lines + local_lines + lrel_lines + cu_lines + mail_lines;
   b->state_words = lines * sw;
+  const uint64_t slot_words = 2ull * slot_layout(nwg, ctx->xcd_count, q.coherent_cs != 0).half();
   hipError_t e = hipMalloc(&b->d_state, b->state_words * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMalloc(&b->d_slots, 2ull * nwg * sizeof(uint32_t));
+  if (e == hipSuccess) e = hipMalloc(&b->d_slots, slot_words * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(b->d_state, 0, b->state_words * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMemset(b->d_slots, 0, 2ull * nwg * sizeof(uint32_t));
+  if (e == hipSuccess) e = hipMemset(b->d_slots, 0, slot_words * sizeof(uint32_t));
   if (e != hipSuccess) {
     ctx->last_hip = (int)e;
     (void)hipFree(b->d_state);
@@ -386,7 +431,8 @@ int sp_barrier_run_hash(sp_barrier* b, uint32_t lanes, uint32_t rounds, uint32_t
   if (coop && spi::capturing(s)) return SP_E_INVAL;
   spi::Resets z;
   z.add(b->d_state, b->state_words);
-  z.add(b->d_slots, 2ull * b->nwg);
+  SlotLayout at = slot_layout(b->nwg, ctx->xcd_count, b->st.fenced == 0);
+  z.add(b->d_slots, 2ull * at.half());
   if (b->d_near) z.add(b->d_near, b->near_words);
   SP_CHECK(spi::begin_timed(ctx, s, z));
   uint64_t timeout = spi::timeout_ticks(ctx, b->p);
@@ -396,7 +442,8 @@ int sp_barrier_run_hash(sp_barrier* b, uint32_t lanes, uint32_t rounds, uint32_t
     SP_HIP(ctx, hipLaunchCooperativeKernel(kern, dim3(N), dim3(lanes), args, 0, s));
   } else {
     sp::BarrierState state = b->st;
-    void* args[] = {&state, &rounds, &seed, &b->d_slots, &out_checksums, &ctx->d_err, &timeout};
+    void* args[] = {&state,         &rounds,     &seed,   &b->d_slots, &at,
+                    &out_checksums, &ctx->d_err, &timeout};
     if (b->p.cooperative)
       SP_HIP(ctx, hipLaunchCooperativeKernel(kern, dim3(N), dim3(lanes), args, 0, s));
     else
