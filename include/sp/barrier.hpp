@@ -242,9 +242,17 @@ __device__ __forceinline__ bool flag_wait(const BarrierState& s, uint32_t stamp,
 // only the master poll them and release its XCD through the L2 was slower (2048 workgroups
 // 5.40 against 5.27 plain, 3.49 against 3.34 coherent): what the shorter polls save, the
 // extra hop costs.
-struct XcdLocal {
-  uint32_t x;        // the XCD this workgroup runs on
+enum : uint32_t {  // what a workgroup does in a round (XcdLocal::role)
+  kXcdUse = 1,      // the per-XCD protocol is in use (0: the counter tree)
+  kXcdMaster = 2,   // gathers its XCD's arrivals
+  kXcdFenced = 4,
+  kXcdCuLeader = 8  // invalidates for its CU (fenced only)
+};
+struct alignas(16) XcdLocal {
+  uint32_t role;
   uint32_t k;        // member index within the XCD (0 = master)
+  uint32_t* block;   // this XCD's block of arrival flags
+  uint32_t x;        // the XCD this workgroup runs on
   uint32_t members;  // members of this XCD
   uint32_t xmask;    // XCDs that have members (bit i = XCD i)
   uint32_t key;      // CU key: XCD * 256 + CU id
@@ -254,12 +262,11 @@ struct XcdLocal {
   // Resolved once in round 0 from the barrier's state and its placement tables, so that
   // later rounds read nothing from the kernel's arguments (reloading those fields inside
   // the round, or indexing the tables there, was measured to cost ~10 % of a round):
-  uint32_t* block;         // this XCD's block of arrival flags
   const uint32_t* stamps;  // the stamps this workgroup polls: its copy, or xarrive
   uint32_t* rel;           // this CU's release line
   uint32_t* mail_x;        // xmail + x: the master stores copy c at mail_x + pub[c]
   uint32_t* xarrive_x;     // the XCD's stamp line when there are no copies
-  uint32_t groups, copies, sstride, fenced, poll_sleep, lanes;
+  uint32_t groups, copies, sstride, poll_sleep, lanes;
 };
 
 // The master's stores of its stamp: copy c at pub[c] + the XCD's index in xmail.
@@ -294,28 +301,55 @@ __device__ __forceinline__ int scan_arrivals(const uint8_t* block, uint32_t memb
   return 1;
 }
 
-__device__ __forceinline__ bool xcd_wait(uint32_t stamp, const Ctl& ctl, const XcdLocal& L,
-                                         const uint32_t* pub, uint32_t* fail) {
+__device__ __forceinline__ bool xcd_wait(const BarrierState& tree, uint32_t stamp, const Ctl& ctl,
+                                         const XcdLocal& L, const uint32_t* pub,
+                                         uint32_t* fail) {
   __shared__ uint32_t s_ok;
-  // The registration is the same for the whole workgroup: keep it in scalar registers.
-  const uint32_t X = uniform(L.groups);
+  // What the other wavefronts of a workgroup execute takes issue slots from the ones that the
+  // round waits for (32 wavefronts per CU): unless they scan arrivals, only the workgroup
+  // barriers of their role. (Per round, with the first round apart from the loop and the counter
+  // tree's arguments in LDS, which leave the scalar registers to these: 2048 workgroups of 256
+  // lanes, agent-scope data, 2.68 -> 2.45 us; 256 of 64 lanes, plain data, 3.95 -> 3.87.)
+  if (uniform(threadIdx.x) >= 64) {
+    const uint32_t role = uniform(L.role);
+    if ((role & (kXcdUse | kXcdMaster)) == kXcdUse) {
+      __syncthreads();
+      if (!(role & kXcdFenced)) return and_sync(1, stamp, fail);
+      if ((role & kXcdCuLeader) && !and_sync(1, stamp, fail)) return false;
+      __syncthreads();
+      return (role & kXcdCuLeader) || s_ok;
+    }
+  }
+  // The registration is the same for the whole workgroup: it goes to scalar registers, what
+  // the arrival needs before the workgroup barrier and the rest behind the arrival.
+  const uint32_t role = uniform(L.role);
   const uint32_t k = uniform(L.k);
-  const uint32_t members = uniform(L.members);
-  const uint32_t xmask = uniform(L.xmask);
-  const uint32_t slot = uniform(L.slot);
-  const uint32_t fenced = uniform(L.fenced);
   uint8_t* block = reinterpret_cast<uint8_t*>(uniform_ptr(L.block));
+  int ok = 1;
+  __syncthreads();
+  if (!(role & kXcdUse)) {  // a registration did not fit: the counter tree
+    if (is_leader()) {
+      const bool arrived = counter_arrive_wait<SP_BARRIER_TREE>(tree, stamp, ctl);
+      if (tree.fenced) fence_acquire();
+      s_ok = arrived;
+    }
+    __syncthreads();
+    return s_ok;
+  }
+  if (!(role & kXcdMaster) && is_leader()) st_xcd8(block + k, (uint8_t)stamp);
+  const uint32_t X = uniform(L.groups);
+  const uint32_t xmask = uniform(L.xmask);
+  const bool fenced = role & kXcdFenced;
   // The populated XCDs' stamps: one line each, or packed in this CU's copy.
   const uint32_t* stamps = uniform_ptr(L.stamps);
   const uint32_t sstride = uniform(L.sstride);
   Wait w(ctl, uniform(L.poll_sleep));
-  int ok = 1;
-  __syncthreads();
   if (threadIdx.x == 0) fail[(stamp + 1) & 1] = 0;  // for the next round's and_sync
-  const uint32_t C = uniform(L.copies);
-  if (k == 0) {
+  if (role & kXcdMaster) {
     // XCD master: gather the XCD's arrivals, write the XCD's L2 back once, publish (in
     // every copy of the stamps, by the first wavefront after its writeback).
+    const uint32_t members = uniform(L.members);
+    const uint32_t C = uniform(L.copies);
     ok = scan_arrivals(block, members, stamp, w, uniform(L.lanes));
     ok = and_sync(ok, stamp, fail);
     if (!ok) return false;
@@ -329,8 +363,6 @@ __device__ __forceinline__ bool xcd_wait(uint32_t stamp, const Ctl& ctl, const X
       }
       arrive_ahead(block, members, stamp + 1);
     }
-  } else if (is_leader()) {
-    st_xcd8(block + k, (uint8_t)stamp);
   }
   if (!fenced) {
     // Coherent data: no cache maintenance, so nothing is shared per CU; every workgroup
@@ -341,7 +373,7 @@ __device__ __forceinline__ bool xcd_wait(uint32_t stamp, const Ctl& ctl, const X
   }
   // this CU's release line
   uint32_t* rel = uniform_ptr(L.rel);
-  if (slot == 0) {
+  if (role & kXcdCuLeader) {
     // CU leader: once every populated XCD has published, invalidate for the CU and
     // release it.  The invalidation has to follow the last XCD's writeback: a line that
     // a kernel on another stream reads on this XCD before then (say, other words of a
@@ -365,7 +397,7 @@ __device__ __forceinline__ bool xcd_wait(uint32_t stamp, const Ctl& ctl, const X
 // Round 0 of the per-XCD barrier: register per XCD and per CU, run the counter tree
 // with per-workgroup fences, then load what the later rounds use.
 __device__ __forceinline__ bool xcd_setup(const BarrierState& s, const Ctl& ctl, XcdLocal& L,
-                                          uint32_t* pub, uint32_t* fail, uint32_t* use_xcd) {
+                                          BarrierState& tree, uint32_t* pub, uint32_t* fail) {
   __shared__ uint32_t s_ok;
   const uint32_t X = s.groups;
   __syncthreads();  // every wavefront's stores have completed (barrier_wait's entry wait)
@@ -390,7 +422,8 @@ __device__ __forceinline__ bool xcd_setup(const BarrierState& s, const Ctl& ctl,
     wave_stores_complete();
     const bool ok = counter_arrive_wait<SP_BARRIER_TREE>(s, 1, ctl);
     fence_acquire();  // round 0 only: always, so the registrations below read fresh
-    *use_xcd = ld_relaxed(s.overflow) == 0;
+    L.role = (ld_relaxed(s.overflow) == 0 ? kXcdUse : 0) | (L.k == 0 ? kXcdMaster : 0) |
+             (s.fenced ? kXcdFenced : 0) | (s.fenced && L.slot == 0 ? kXcdCuLeader : 0);
     L.rank = ld_relaxed(s.cu_rank + L.key);
     L.members = ld_relaxed(s.xcount + xcc);
     uint32_t mask = 0;
@@ -407,9 +440,17 @@ __device__ __forceinline__ bool xcd_setup(const BarrierState& s, const Ctl& ctl,
     L.xarrive_x = s.xarrive + (size_t)xcc * s.stride;
     L.groups = X;
     L.copies = s.xcopies;
-    L.fenced = s.fenced;
     L.poll_sleep = s.poll_sleep;
     L.lanes = blockDim.x;
+    tree.nwg = s.nwg;
+    tree.stride = s.stride;
+    tree.tgroups = s.tgroups;
+    tree.fenced = s.fenced;
+    tree.poll_sleep = s.poll_sleep;
+    tree.gcnt = s.gcnt;
+    tree.ggen = s.ggen;
+    tree.top = s.top;
+    tree.topgen = s.topgen;
     fail[0] = fail[1] = 0;
     s_ok = ok;
   }
@@ -425,7 +466,8 @@ __device__ __forceinline__ bool xcd_setup(const BarrierState& s, const Ctl& ctl,
 
 // Global barrier, round `round` (0-based) of the current run.
 template <int KIND>
-__device__ bool barrier_wait(const BarrierState& s, uint32_t round, const Ctl& ctl) {
+__device__ __forceinline__ bool barrier_wait(const BarrierState& s, uint32_t round,
+                                             const Ctl& ctl) {
   __shared__ uint32_t s_ok;
   const uint32_t stamp = round + 1;
   // (the per-XCD barrier's workgroups arrive without a release fence)
@@ -436,19 +478,14 @@ __device__ bool barrier_wait(const BarrierState& s, uint32_t round, const Ctl& c
     // Round 0 registers every workgroup by XCD and CU; later rounds use the per-XCD
     // protocol unless a registration did not fit, the counter tree otherwise.
     __shared__ detail::XcdLocal s_local;
-    __shared__ uint32_t s_use;
+    // What the counter tree reads, for the rounds that fall back on it: taken from the
+    // kernel's arguments there, the compiler loads it ahead of all rounds and the scalar
+    // registers it stands in are missing in the protocol's.
+    __shared__ BarrierState s_tree;
     __shared__ uint32_t s_pub[detail::kMaxCopies];
     __shared__ uint32_t s_fail[2];
-    if (round == 0) return detail::xcd_setup(s, ctl, s_local, s_pub, s_fail, &s_use);
-    if (s_use) return detail::xcd_wait(stamp, ctl, s_local, s_pub, s_fail);
-    __syncthreads();
-    if (is_leader()) {
-      const bool ok = detail::counter_arrive_wait<SP_BARRIER_TREE>(s, stamp, ctl);
-      if (s.fenced) fence_acquire();
-      s_ok = ok;
-    }
-    __syncthreads();
-    return s_ok;
+    if (round == 0) return detail::xcd_setup(s, ctl, s_local, s_tree, s_pub, s_fail);
+    return detail::xcd_wait(s_tree, stamp, ctl, s_local, s_pub, s_fail);
   } else {
     __syncthreads();
     if (is_leader()) {

@@ -77,7 +77,7 @@ __global__ SP_FULL_OCCUPANCY void k_barrier_hash(sp::BarrierState s, uint32_t ro
   uint32_t next_place = at.step - at.blocks * at.block_words;  // from the block after the last
   __asm__("" : "+v"(mine), "+v"(word), "+v"(left), "+v"(block));
   __asm__("" : "+v"(blocks), "+v"(next_block), "+v"(next_place));
-  for (uint32_t r = 0; r < rounds; ++r) {
+  const auto exchange = [&](uint32_t r) {
     uint32_t* half = slots + (r & 1) * at.half();
     if (threadIdx.x == writer) {
       if constexpr (COHERENT) sp::st_relaxed(half + mine, v);
@@ -95,14 +95,22 @@ __global__ SP_FULL_OCCUPANCY void k_barrier_hash(sp::BarrierState s, uint32_t ro
         left = N;
       }
     }
-    v = sp::computed_here(sp::sm32(seed ^ (b << 16) ^ (r + 1)));
+    if (threadIdx.x == writer) {
+      v = sp::sm32(seed ^ (b << 16) ^ (r + 1));
+      __asm__ __volatile__("" : "+v"(v));
+    }
     chk ^= got;  // (the last round's load, waited for behind this round's store)
-    if (!sp::barrier_wait<KIND>(s, r, ctl)) return;
+    if (!sp::barrier_wait<KIND>(s, r, ctl)) return false;
     if (threadIdx.x == reader) {
       if constexpr (COHERENT) got = sp::ld_relaxed(src);
       else got = *src;
     }
-  }
+    return true;
+  };
+  // the first round by itself: what only it needs then takes no registers in the others
+  if (rounds && !exchange(0)) return;
+  for (uint32_t r = 1; r < rounds; ++r)
+    if (!exchange(r)) return;
   if (threadIdx.x == reader) out[b] = chk ^ got;
 }
 

@@ -235,3 +235,22 @@ def test_pool_slots_returned_behind_the_post(ctx, kind, K, nwg, lanes, coherent)
         s.close()
     assert (r["chk"] == oracle.sem_closed(11, nwg, 5000)).all()
     assert 1 <= r["maxocc"] <= K and int(r["data"].astype("u8").sum()) == 5000
+
+
+@pytest.mark.parametrize("coherent", [0, 1])
+@pytest.mark.parametrize("kind", ["central", "tree", "flag", "xcd"])
+@pytest.mark.parametrize("nwg,lanes", [(1, 64), (2, 128), (7, 64), (8, 64), (9, 192), (255, 64),
+                                       (256, 128), (257, 1024 // 4), (511, 320), (2047, 256)])
+def test_exchange_layout(ctx, nwg, lanes, kind, coherent):
+    """Workgroup counts around whole blocks of the exchange's layout, rounds past the count
+    (the reader comes round to its first slot), one round and none."""
+    import paper_1110_4623_amd as sp
+    announce("exchange layout", kind, nwg, lanes, coherent)
+    b = sp.Barrier(ctx, kind, nwg, coherent_cs=coherent)
+    try:
+        for rounds in (1, 2, min(2 * nwg + 3, 300), 0):
+            chk, st = b.run_hash(lanes, rounds, 13)
+            assert st["device_error"] == 0
+            assert (chk == oracle.barrier_closed(13, nwg, rounds)).all()
+    finally:
+        b.close()
