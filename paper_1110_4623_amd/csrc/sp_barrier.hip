@@ -174,6 +174,9 @@ const void* barrier_kernel(uint32_t kind, bool coherent) {
 constexpr uint32_t kChunkWords = 2048;  // 8 KiB
 constexpr uint32_t kNearChunks = 64;    // 512 KiB
 constexpr uint32_t kProbeWorkgroups = 64;
+// Near and far chunks differ by 300 clocks in 700-1000, so a mean of 24 tells them apart; the
+// probe is most of a barrier's creation (32 rounds: 1.8-1.9 ms).
+constexpr uint32_t kProbeRounds = 24;
 
 __global__ void k_near_probe(uint32_t* area, uint32_t nchunks, uint32_t groups,
                              uint32_t rounds, uint32_t* claims, uint32_t* lat,
@@ -188,14 +191,18 @@ __global__ void k_near_probe(uint32_t* area, uint32_t nchunks, uint32_t groups,
     uint32_t* ping = area + (size_t)j * kChunkWords + x * 64;  // two lines per XCD
     uint32_t* pong = ping + 32;
     const uint64_t t0 = sp::shader_clock();
+    // (the clock is read every 64 polls: it takes about as long as a poll)
+    const auto seen = [&](const uint32_t* p, uint32_t v) {
+      for (uint32_t n = 1; sp::uniform(sp::ld_relaxed(p)) < v; ++n)
+        if ((n & 63) == 0 && sp::wall_clock() > end) return false;
+      return true;
+    };
     for (uint32_t r = 0; r < rounds; ++r) {
       if (role == 0) {
         sp::st_relaxed(ping, 2 * r + 1);
-        while (sp::ld_relaxed(pong) < 2 * r + 2)
-          if (sp::wall_clock() > end) return;
+        if (!seen(pong, 2 * r + 2)) return;
       } else {
-        while (sp::ld_relaxed(ping) < 2 * r + 1)
-          if (sp::wall_clock() > end) return;
+        if (!seen(ping, 2 * r + 1)) return;
         sp::st_relaxed(pong, 2 * r + 2);
       }
     }
@@ -223,7 +230,7 @@ int place_near(sp_barrier* b, uint32_t G, bool mail, bool rel) {
   SP_CHECK(spi::fill_u32(ctx, b->d_near, b->near_words, 0, s));
   const uint64_t deadline = (uint64_t)ctx->wall_khz * 50;  // 50 ms
   hipLaunchKernelGGL(k_near_probe, dim3(kProbeWorkgroups), dim3(64), 0, s, b->d_near,
-                     kNearChunks, G, 32u, claims, lat, deadline);
+                     kNearChunks, G, kProbeRounds, claims, lat, deadline);
   SP_HIP(ctx, hipGetLastError());
   SP_HIP(ctx, hipStreamSynchronize(s));
   std::vector<uint32_t> h((size_t)G * kNearChunks);
