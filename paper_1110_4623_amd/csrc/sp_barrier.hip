@@ -40,13 +40,18 @@ struct SlotLayout {
 // back by one XCD, whole, and one XCD's readers of a round want one block.  Agent-scope
 // values: a line each, since accesses to one line take their turns (32 workgroups' stores
 // and 32 loads of them took most of a 1.1 us exchange).
+// Where every one of many workgroups fences for itself (plain values, other kinds), the packed
+// array stays: flag barrier, 1024 / 2048 workgroups, 20.4 / 38.4 us against 24.8 / 46.3 with
+// blocks, counter tree 18.5 / 34.5 against 20.4 / 36.2; up to 64 workgroups blocks are no
+// slower (central, 48 and 64: 3.1 / 3.7 against 3.5 / 4.3).
 // Per round, packed array -> this: 16 workgroups, central barrier, 1.75 -> 1.72 us, agent-scope
 // values 1.86 -> 1.38; 1024 of 256 lanes 4.76 -> 4.43, 2.89 -> 2.24; 2048 of 256 lanes
 // 5.13 -> 4.81, 3.22 -> 2.68.
-SlotLayout slot_layout(uint32_t nwg, uint32_t xcds, bool coherent) {
+SlotLayout slot_layout(uint32_t kind, uint32_t nwg, uint32_t xcds, bool coherent) {
   const uint32_t most = 1u << 16;  // (more workgroups than can run: no room for lines)
   SlotLayout at;
-  at.blocks = std::max<uint32_t>(1, xcds);
+  const bool by_xcd = coherent || kind == SP_BARRIER_XCD || nwg <= 64;
+  at.blocks = by_xcd ? std::max<uint32_t>(1, xcds) : 1;
   at.step = coherent && nwg <= most ? 32 : 1;
   at.block_words = ((nwg + at.blocks - 1) / at.blocks * at.step + 31) / 32 * 32;
   return at;
@@ -318,7 +323,7 @@ int sp_barrier_create(sp_ctx* ctx, uint32_t kind, uint32_t nwg, const sp_params*
   const uint64_t lines =
       5 + 3ull * G + 2 * flag_lines + local_lines + lrel_lines + cu_lines + mail_lines;
   b->state_words = lines * sw;
-  const uint64_t slot_words = 2ull * slot_layout(nwg, ctx->xcd_count, q.coherent_cs != 0).half();
+  const uint64_t slot_words = 2ull * slot_layout(kind, nwg, ctx->xcd_count, q.coherent_cs != 0).half();
   hipError_t e = hipMalloc(&b->d_state, b->state_words * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMalloc(&b->d_slots, slot_words * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(b->d_state, 0, b->state_words * sizeof(uint32_t));
@@ -446,7 +451,7 @@ int sp_barrier_run_hash(sp_barrier* b, uint32_t lanes, uint32_t rounds, uint32_t
   if (coop && spi::capturing(s)) return SP_E_INVAL;
   spi::Resets z;
   z.add(b->d_state, b->state_words);
-  SlotLayout at = slot_layout(b->nwg, ctx->xcd_count, b->st.fenced == 0);
+  SlotLayout at = slot_layout(b->kind, b->nwg, ctx->xcd_count, b->st.fenced == 0);
   z.add(b->d_slots, 2ull * at.half());
   if (b->d_near) z.add(b->d_near, b->near_words);
   SP_CHECK(spi::begin_timed(ctx, s, z));
