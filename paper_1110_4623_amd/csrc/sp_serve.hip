@@ -58,12 +58,18 @@ __device__ __forceinline__ void st_sys(uint32_t* p, uint32_t v) {
 // inputs through readfirstlane makes them wave-uniform, so the serial chain runs on the
 // scalar ALU (one instruction per dependent step) instead of as one-lane vector
 // instructions with quarter-rate 32-bit multiplies.  Both the persistent kernel and the
-// launch comparator use this routine.
+// launch comparator use this routine.  The chain's own latency bounds a long request, and a
+// taken branch costs a refetch that depends on where the loop lies: 16 steps per iteration
+// make that small (p99 at 10^5 requests/s with 4 / 8 / 16 / 32 steps: 98-106, 92, 85, 85 us).
+constexpr uint32_t kChainSteps = 16;
 __device__ __forceinline__ uint32_t chain(uint32_t x, uint32_t L) {
   x = __builtin_amdgcn_readfirstlane(x);
   L = __builtin_amdgcn_readfirstlane(L);
   uint32_t i = 0;
-  for (; i + 4 <= L; i += 4) x = sp::sm32(sp::sm32(sp::sm32(sp::sm32(x))));
+  for (; i + kChainSteps <= L; i += kChainSteps) {
+#pragma unroll
+    for (uint32_t k = 0; k < kChainSteps; ++k) x = sp::sm32(x);
+  }
   for (; i < L; ++i) x = sp::sm32(x);
   return x;
 }

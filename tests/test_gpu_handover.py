@@ -254,3 +254,21 @@ def test_exchange_layout(ctx, nwg, lanes, kind, coherent):
             assert (chk == oracle.barrier_closed(13, nwg, rounds)).all()
     finally:
         b.close()
+
+
+@pytest.mark.parametrize("mode", ["persistent", "launch"])
+def test_chain_lengths_around_an_iteration(ctx, mode):
+    """Hash chains of every length from none to four iterations of the unrolled loop."""
+    import numpy as np
+
+    import paper_1110_4623_amd as sp
+    import sp_inputs
+    announce("chain lengths", mode)
+    reqs = dict(sp_inputs.request_table(66, 1e5, 9))
+    reqs["L"] = np.arange(66, dtype=np.asarray(reqs["L"]).dtype)
+    if mode == "persistent":
+        out, _, r = sp.serve(ctx, reqs, nwg=32, seed=9)
+    else:
+        out, _, r = sp.serve_launch_per_request(ctx, reqs, seed=9)
+    assert r["completed"] == 66
+    assert (out == oracle.chain_batch(9, reqs["L"])).all()
