@@ -291,7 +291,7 @@ int sp_init(int device, sp_ctx** out) {
     }
   ctx->defaults[0][0].kind = SP_BARRIER_CENTRAL;  // 1.7 us/round at 16 workgroups
   ctx->defaults[0][0].p.poll_sleep = 0;
-  ctx->defaults[0][1].kind = SP_BARRIER_XCD;      // 6.1 us/round at 1024, 64 stamp copies
+  ctx->defaults[0][1].kind = SP_BARRIER_XCD;      // 4.4 us/round at 1024, 64 stamp copies
   ctx->defaults[0][1].p.poll_sleep = 0;
   // paper's linear backoff, I_max 8: 0.62 / 0.74 M/s at 4 / 32 workgroups on one lock
   // (cohort lock 0.52 / 0.84, ticket 0.57 / 0.68)
@@ -299,15 +299,14 @@ int sp_init(int device, sp_ctx** out) {
   ctx->defaults[1][0].p.backoff = SP_BACKOFF_PAPER;
   ctx->defaults[1][0].p.backoff_max = 8;
   // CU-cohort lock (the XCD-cohort lock below two contenders per CU and lock): one lock
-  // 1.13 M/s at 2048 workgroups, 1.18 at 1024 (XCD-cohort lock 0.74 / 0.77, ticket 0.65);
-  // 16 locks at 2048 run the XCD-cohort lock, 13.1 M/s (array 9.2)
+  // 1.57 M/s at 2048 workgroups, 1.60 at 1024 (XCD-cohort lock 1.00, ticket 0.70); 16 locks
+  // at 2048 run the XCD-cohort lock, 17.1 M/s (array 11.2)
   ctx->defaults[1][1].kind = SP_MUTEX_CU_COHORT;
   ctx->defaults[1][1].p.poll_sleep = 0;
   ctx->defaults[1][1].p.cohort_passes = 64;
   // per-XCD chains (K below the XCD count: one set of chains; K above 4096 per XCD: the
-  // array kind): 20.8 M pairs/s K = 32 at 256, 126 M K = 256 at 2048 (one set of chains
-  // 18.6 / 57.7); 20.3 M K = 32 at 2048, 2.31 M K = 4 (chains 17.9 / 2.31, adaptive
-  // 6.3 / 1.55)
+  // array kind): 28.7 M pairs/s K = 32 at 256, 134 M K = 256 at 2048; 28.2 M K = 32 at 2048,
+  // 2.62 M K = 4 (one set of chains 20.0 / 2.62, adaptive 6.75 at K = 32)
   ctx->defaults[2][0].kind = SP_SEM_XCD_CHAIN;
   ctx->defaults[2][0].p.poll_sleep = 0;
   ctx->defaults[2][1].kind = SP_SEM_XCD_CHAIN;

@@ -72,8 +72,7 @@ __global__ SP_FULL_OCCUPANCY void k_barrier_hash(sp::BarrierState s, uint32_t ro
   uint32_t chk = 0, got = 0;
   // What a round stores and where it reads are found before its barrier, so that after it
   // only the load and the next store stand on the way to the next one (a 64-bit remainder
-  // and a hash there cost 0.1-0.2 us: 2048 workgroups 5.18 us per round from 5.27, 1000 of
-  // 192 lanes, coherent data, 2.81 from 3.06).
+  // and a hash there cost 0.1-0.2 us per round).
   uint32_t v = sp::sm32(seed ^ (b << 16));
   // the writer's place, and the reader's, which walks the layout one workgroup a round; in
   // vector registers, which are plenty (the per-XCD barrier takes all the scalar ones)
