@@ -55,11 +55,11 @@ __device__ __forceinline__ void cond_signal_leader(const CondState& cv) {
   }
 }
 
-// A signal in three steps, for a leader that holds the mutex and has other round trips to
-// make: cond_peek loads the counters beside the protected data, cond_signal_begin releases
-// the next ticket if one waits, and cond_signal_end, best after the unlock, looks at what
-// that found (a signaller that does not hold the mutex came between: then once more, which
-// without the mutex is a signal too, only a later one).
+// A signal in two steps, for a condition variable whose signallers all hold the mutex:
+// cond_peek loads the counters beside the protected data, and cond_signal_held releases the
+// next ticket, if one waits, with a store (nobody else writes the counter meanwhile; the
+// unlock waits for a store's acknowledgement 0.1 us less than for a compare-and-swap on a word
+// that waiters poll).
 struct CondPeek {
   uint32_t signals, waiters;
 };
@@ -69,13 +69,8 @@ __device__ __forceinline__ CondPeek cond_peek(const CondState& cv) {
   k.waiters = ld_relaxed(cv.waiters);
   return k;
 }
-__device__ __forceinline__ uint32_t cond_signal_begin(const CondState& cv, const CondPeek& k) {
-  if ((int32_t)(k.waiters - k.signals) <= 0) return k.signals;
-  return cas_relaxed(cv.signals, k.signals, k.signals + 1);
-}
-__device__ __forceinline__ void cond_signal_end(const CondState& cv, const CondPeek& k,
-                                                uint32_t seen) {
-  if (seen != k.signals) cond_signal_leader(cv);
+__device__ __forceinline__ void cond_signal_held(const CondState& cv, const CondPeek& k) {
+  if ((int32_t)(k.waiters - k.signals) > 0) st_relaxed(cv.signals, k.signals + 1);
 }
 
 __device__ __forceinline__ void cond_broadcast_leader(const CondState& cv) {

@@ -26,13 +26,13 @@ constexpr uint32_t kLine = 32;  // words per 128-byte line
 //
 // What bounds it is the chain of one operation under the mutex: hand-over, state, stores,
 // writeback.  The state words share a line and come with one miss, beside the condition
-// variable's counters; the signal is in flight during the stores and the writeback and is
-// looked at after the unlock; ring indices wrap without a division; the value put is found
-// before the lock, the value taken is used after it.  The signal stays ahead of the unlock:
+// variable's counters; the signal is a store beside the data's (a compare-and-swap there took
+// 3-6 % more); ring indices wrap without a division; the value put is found before the lock,
+// the value taken is used after it.  The signal stays ahead of the unlock:
 // after it, a signaller came back for the mutex before the workgroup it woke, found nothing
 // to do and waited in its turn (2 workgroups, capacity 1: 3.2 -> 6.0 us per item).
-// 256 workgroups, 96 producers, capacity 64, ticket mutex: 4.96 -> 4.0 us per item; cohort
-// mutex 4.29 -> 2.82.
+// 256 workgroups, 96 producers, capacity 64, ticket mutex: 4.96 -> 3.8 us per item; cohort
+// mutex 4.29 -> 2.80.
 template <int MKIND>
 __global__ SP_FULL_OCCUPANCY void k_bounded_buffer(sp::MutexState m, sp::CondState not_full,
                                                    sp::CondState not_empty, uint32_t* bstate,
@@ -62,7 +62,6 @@ __global__ SP_FULL_OCCUPANCY void k_bounded_buffer(sp::MutexState m, sp::CondSta
     if (!sp::mutex_lock<MKIND>(m, 0, ctl, &hold)) return;
     uint32_t count, head, tail, most;
     sp::CondPeek peek;
-    uint32_t seen;
     for (;;) {
       if (sp::is_leader()) {
         peek = sp::cond_peek(other);
@@ -77,7 +76,7 @@ __global__ SP_FULL_OCCUPANCY void k_bounded_buffer(sp::MutexState m, sp::CondSta
       if (!sp::cond_wait<MKIND>(mine, m, 0, &hold, ctl)) return;
     }
     if (sp::is_leader()) {
-      seen = sp::cond_signal_begin(other, peek);
+      sp::cond_signal_held(other, peek);
       if (prod) {
         buf[tail] = v;
         bstate[B_TAIL] = tail + 1 == capacity ? 0 : tail + 1;
@@ -90,13 +89,10 @@ __global__ SP_FULL_OCCUPANCY void k_bounded_buffer(sp::MutexState m, sp::CondSta
       }
     }
     sp::mutex_unlock<MKIND>(m, 0, &hold);
-    if (sp::is_leader()) {
-      sp::cond_signal_end(other, peek, seen);
-      if (!prod) {
-        x ^= v;
-        sum += v;
-        if (taken) taken[first + j] = v;
-      }
+    if (!prod && sp::is_leader()) {
+      x ^= v;
+      sum += v;
+      if (taken) taken[first + j] = v;
     }
     ++done;
   }
