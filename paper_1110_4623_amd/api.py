@@ -119,6 +119,15 @@ class Context:
             return self.torch.zeros(max(count, 1), dtype=tdt, device="cuda")
         return DeviceBuffer(self, max(count, 1) * size)
 
+    def _output(self, count: int, dtype: str = "u32"):
+        """A device array that the next call writes whole: not cleared first, which would be
+        a launch of its own (5 of 55 us of a small read).  Cleared all the same while a graph
+        is recorded, when the call writes nothing yet."""
+        if self.torch is None or getattr(self, "_record_stream", None) is not None:
+            return self.zeros(count, dtype)
+        tdt = {"u32": self.torch.int32, "u64": self.torch.int64}[dtype]
+        return self.torch.empty(count, dtype=tdt, device="cuda")
+
     def upload(self, arr: np.ndarray):
         arr = np.ascontiguousarray(arr)
         if self.torch is not None:
@@ -383,7 +392,7 @@ def bounded_buffer(ctx: Context, mutex_kind: str, nwg: int, producers: int, capa
     """Producer/consumer ring on a mutex and two condition variables
     (sp_cond_run_bounded_buffer, or with noalloc=True the allocation-free
     sp_cond_run_bounded_buffer_noalloc).  values=True also returns every value taken."""
-    out = ctx.zeros(6, "u64")
+    out = ctx._output(6, "u64")
     taken = ctx.zeros(items) if values else None
     p = make_params(**params)
     st = N.Stats()
@@ -460,7 +469,7 @@ def bench_atomic(ctx: Context, op: str, nwg: int, lanes: int, T: int, stride: in
     words = T * stride // 4
     if buf is None:
         buf = ctx.zeros(words)
-    out = ctx.zeros(1, "u64")
+    out = ctx._output(1, "u64")
     st = N.Stats()
     check(lib.sp_bench_atomic(ctx.h, N.OPS[op], nwg, lanes, T, stride, N.ISSUE[mode], n,
                               seed & 0xFFFFFFFF, ctx.ptr(perm), ctx.ptr(buf), ctx.ptr(out),
@@ -484,7 +493,7 @@ def paper12(ctx: Context, test: str, nwg: int, lanes: int = 64, n_ops: int = 100
 
 
 def stream_read(ctx: Context, buf, nbytes: int, reps: int = 1, nwg: int = 0):
-    out = ctx.zeros(1, "u64")
+    out = ctx._output(1, "u64")
     st = N.Stats()
     check(lib.sp_bench_stream(ctx.h, ctx.ptr(buf), nbytes, nwg, reps, ctx.ptr(out),
                               ctypes.byref(st), ctx.stream()), "sp_bench_stream", ctx.h)
