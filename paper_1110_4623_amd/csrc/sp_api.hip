@@ -48,6 +48,25 @@ __global__ void k_finish(const uint32_t* err, uint32_t* h_err, const unsigned lo
   *out += v;
 }
 
+// Workgroups of `waves` wavefronts that a CU is sure to hold at once with `slots` wave slots
+// on each of its four SIMDs.  Not slots * 4 / waves: the dispatcher starts a workgroup of more
+// than four wavefronts only where every SIMD has room for its share rounded up, and the
+// workgroups before it need not lie evenly, so slots stay empty.  Measured with workgroups that
+// spin for a fixed time and never wait for each other, 20 grids per point after kernels of
+// other shapes: at 8 slots 5 wavefronts fit 5 times on every CU and a sixth waited for an end
+// on 253-256 CUs; 6 fit 4 times (a fifth waited on up to 128 CUs in 7 of 20 grids), 10 twice.
+// The line below, with one wavefront more on the fullest SIMD where uneven placements were
+// seen, is the largest count that never waited at all 100 points measured (1-16 wavefronts,
+// 2-8 slots).
+uint32_t workgroups_by_wave_slots(uint32_t waves, uint32_t slots) {
+  if (waves <= 2) return 4 * slots / waves;
+  const uint32_t share = (waves + 3) / 4, over = waves % 4;
+  for (uint32_t n = 0;; ++n) {
+    const uint32_t uneven = (over == 1 && n >= 3) || (over == 2 && n >= 2);
+    if ((n * waves + 3) / 4 + uneven + share > slots) return n;
+  }
+}
+
 __global__ void k_probe_xcc(uint32_t* out) {
   if (threadIdx.x == 0) out[blockIdx.x] = sp::xcc_id();
 }
@@ -205,7 +224,7 @@ uint32_t sp_resident_per_cu(const sp_occupancy* occ) {
     const uint32_t v = (occ->vgprs + kVgprGranule - 1) / kVgprGranule * kVgprGranule;
     per_simd = std::min(per_simd, kVgprsPerSimd / v);
   }
-  uint32_t wgs = kSimds * per_simd / waves;
+  uint32_t wgs = workgroups_by_wave_slots(waves, per_simd);
   if (occ->lds_bytes > 0) {
     const uint32_t l = (occ->lds_bytes + kLdsGranule - 1) / kLdsGranule * kLdsGranule;
     wgs = std::min(wgs, kLdsBytes / l);
