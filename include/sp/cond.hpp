@@ -33,7 +33,7 @@ __device__ bool cond_wait(const CondState& cv, const MutexState& m, uint32_t loc
   __shared__ uint32_t s_ok;
   uint32_t t = 0;
   if (is_leader()) t = add_relaxed(cv.waiters, 1);
-  mutex_unlock<MKIND, FENCED>(m, lock, hold);
+  mutex_unlock<MKIND, FENCED>(m, lock, hold, &ctl);
   if (is_leader()) {
     Wait w(ctl, cv.poll_sleep);
     s_ok = poll(w, [&] { return (int32_t)uniform(ld_relaxed(cv.signals) - t) > 0; });

@@ -43,6 +43,7 @@ struct MutexHold {
   uint32_t cu_pass;     // SP_MUTEX_CU_COHORT: at entry, a later CU ticket was announced and
                         // the CU's session may grow
   uint32_t* cu;         // SP_MUTEX_CU_COHORT: the grant line of the holder's CU
+  Ctl ctl;              // SP_MUTEX_CU_COHORT: what bounds the lock's wait, and the unlock's
 };
 
 // Cohort lock state of `lock` for the XCD with XCC id x (kXccSlots per lock: the XCC id
@@ -344,6 +345,7 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
       hold->cu_session = kc;
       hold->cu_pass = kc + 1 < s.cohort_bound && (int32_t)(uniform(v.y) - (tc + 1)) > 0;
       hold->cu = line;
+      hold->ctl = ctl;
     } else if constexpr (KIND == SP_MUTEX_MCS) {
       uint32_t* node = mcs_node(s, lock, blockIdx.x);
       st_relaxed(node, 0);      // next: none
@@ -373,8 +375,12 @@ __device__ bool mutex_lock(const MutexState& s, uint32_t lock, const Ctl& ctl,
 
 // `hold`: the record mutex_lock filled in (leader's copy).  It may be nullptr except for
 // SP_MUTEX_ARRAY, SP_MUTEX_COHORT and SP_MUTEX_CU_COHORT (whose mutex_lock needs it too):
-// the ticket and ring mutexes then load turn / head to find the value to publish.  `ctl` bounds SP_MUTEX_MCS's wait for a successor that
-// has taken the tail but not linked in yet (no other kind waits in unlock).
+// the ticket and ring mutexes then load turn / head to find the value to publish.  Two kinds
+// wait in unlock.  SP_MUTEX_MCS waits for a successor that has taken the tail but not linked
+// in yet, which it does with its next instructions; `ctl` bounds that.  SP_MUTEX_CU_COHORT
+// waits for the earlier holders of its CU to count themselves complete, which one that the
+// watchdog ended never does; that wait is bounded by the control block its lock was called
+// with (or by `ctl`).
 template <int KIND, bool FENCED = true>
 __device__ void mutex_unlock(const MutexState& s, uint32_t lock, const MutexHold* hold = nullptr,
                              const Ctl* ctl = nullptr) {
@@ -440,9 +446,9 @@ __device__ void mutex_unlock(const MutexState& s, uint32_t lock, const MutexHold
     if (!is_leader()) return;
     if constexpr (FENCED) {
       uint32_t* done = line + s.qstride;
-      Wait w(ctl ? *ctl : Ctl{nullptr, 0}, 0);
+      Wait w(ctl ? *ctl : hold->ctl, 0);
       while (uniform(ld_cu(done)) != uniform(tc))
-        if (ctl && !w.tick()) return;
+        if (!w.tick()) return;
       if (!pass)
         detail::cohort_release<FENCED>(s, lock, xcc_id(), drawn, hold->ticket,
                                        hold->session + 1, hold->global);
