@@ -13,6 +13,8 @@
 //            next one with a compare-and-swap; a signal with nobody waiting has no effect.
 // broadcast: release every drawn ticket (signals = waiters).
 // Waiters wake in ticket order.  Counters wrap; comparisons are signed differences.
+// Under SP_MUTEX_CU_COHORT a registration or a signal may be in flight when a holder on the
+// same CU enters; its accesses to the same counter come after it (mutex.hpp).
 #pragma once
 
 #include "mutex.hpp"

@@ -204,6 +204,15 @@ __device__ __forceinline__ uint32_t* mcs_node(const MutexState& s, uint32_t lock
 //                         no wait for the stores (mutex_unlock), no load of the record.
 //                         One lock, 16 words, 2048 workgroups: 1.54 M acquisitions/s, from
 //                         1.14 with the stores awaited and the record loaded apart.
+//                         What a fenced section still has in flight when it passes within
+//                         the CU, its agent-scope stores and atomics too (a counter beside
+//                         the data, a condition variable's words), the next holder follows
+//                         through the CU's one request queue to each L2 channel: it sees
+//                         them in everything it accesses at the same addresses.  That is
+//                         the order that workgroup scope stands for on this GPU, where a
+//                         workgroup-scope release waits for no vector memory operation.
+//                         It says nothing to observers on other CUs that do not take the
+//                         lock; before the lock leaves the CU all of it has completed.
 //   SP_MUTEX_MCS          MCS queue lock: each workgroup has a node per lock (next, locked)
 //                         in its own line; lock stores next = none and locked = 1, then
 //                         exchanges the lock word (the queue's tail) with its node id;

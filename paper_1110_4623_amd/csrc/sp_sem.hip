@@ -51,6 +51,9 @@ constexpr uint32_t kCohortSlots = 4096;
 // tracker's words instead of three and waits for one instead of two.
 // 2048 workgroups, K = 32, 2^18 tracked pairs: 16.4 ms against 17.1; 257 workgroups, K = 4,
 // 2^14 pairs with the pool: 11.8 ms against 12.8.
+// K = 1 under the CU-cohort lock posts with the tracker's decrement in flight, and a holder on
+// the same CU increments the word behind it (mutex.hpp): at most one is ever counted.  Awaiting
+// the decrement first took 9.70 ms against 8.87 (2048 workgroups, 8000 pairs).
 // The slot's return is on its way when the unit is posted: a next holder that comes before it
 // finds the slot taken and looks on (257 workgroups, K = 4: 9.8 ms against 11.1).  Loading
 // the owners of several slots beside the first compare-and-swap was slower than trying one
