@@ -570,6 +570,60 @@ class CondModel:
         return None
 
 
+class CondHeldSignalModel(CondModel):
+    """The bounded buffer's signal in two steps, both while its workgroup holds the mutex:
+    with the predicate it loads the other variable's counters; when it acts it first stores
+    signals + 1, as loaded, if a waiter was registered (no compare-and-swap: nobody else
+    writes the counter meanwhile).
+    mutant 'store_unlocked': the store comes after the unlock, so it can bring the counter
+    back to an older value or name a waiter that another signal has released;
+    mutant 'peek_unlocked': the counters are loaded before the mutex is taken."""
+
+    (LOCK, CHECK, REG, UNLOCK_W, POLL, RELOCK, SIGNAL, ACT, UNLOCK, DONE, PEEK, LATE) = range(12)
+
+    def init(self):
+        start = self.PEEK if self.mutant == "peek_unlocked" else self.LOCK
+        return (0, 0, 0, (0, 0), (0, 0)), tuple((start, 0, 0, None) for _ in range(self.n))
+
+    def step(self, a, sh, lo):
+        mutex, count, inside, W, S = sh
+        pc, j, t, peek = lo
+        prod = a < self.P
+        cv_sig = 1 if prod else 0
+
+        def signal():
+            return tuple(peek[0] + 1 if i == cv_sig and peek[1] > peek[0] else v
+                         for i, v in enumerate(S))
+
+        def finished():
+            if j + 1 >= self.quota[a]:
+                return (self.DONE, j + 1, 0, None)
+            return (self.PEEK if self.mutant == "peek_unlocked" else self.LOCK, j + 1, 0, None)
+
+        if pc == self.PEEK:
+            return sh, (self.LOCK, j, t, (S[cv_sig], W[cv_sig]))
+        if pc == self.CHECK:
+            if self.mutant != "peek_unlocked":
+                peek = (S[cv_sig], W[cv_sig])
+            if count == self.C if prod else count == 0:
+                return sh, (self.REG, j, t, peek)
+            return sh, (self.ACT if self.mutant == "store_unlocked" else self.SIGNAL, j, t, peek)
+        if pc == self.SIGNAL:
+            return (mutex, count, inside, W, signal()), (self.ACT, j, t, peek)
+        if pc == self.ACT:
+            return ((mutex, count + 1 if prod else count - 1, inside, W, S),
+                    (self.UNLOCK, j, t, peek))
+        if pc == self.UNLOCK:
+            sh2 = (0, count, inside - 1, W, S)
+            return sh2, ((self.LATE, j, t, peek) if self.mutant == "store_unlocked"
+                         else finished())
+        if pc == self.LATE:
+            return (mutex, count, inside, W, signal()), finished()
+        # lock, registration, wait and relock are CondModel's
+        sh2, lo2 = super().step(a, sh, (pc, j, t))
+        return sh2, lo2 + (peek,)
+
+
 # ------------------------------------------------------------------------------------
 # Semaphores with initial value K.  Each agent performs `ops` wait/post pairs with an
 # occupancy counter incremented on entry and decremented on exit.
@@ -997,7 +1051,10 @@ class CuCohortLockModel:
     mutant 'no_acquire': the holder that took the XCD lock keeps its caches;
     mutant 'group_by_xcd': the groups are the XCDs (a CU id read wrongly), so a pass
     within a group can cross CUs without an acquire;
-    mutant 'no_waiter_check': pass within the group with no later ticket announced."""
+    mutant 'no_waiter_check': pass within the group with no later ticket announced.
+
+    A section's store is complete before its holder grants, as sections of agent-scope
+    accesses are; CuCohortEarlyGrantModel has the hand-over of plain sections."""
 
     (DRAW_C, ANN, POLL_C, DRAW_X, POLL_X, DRAW_G, POLL_G, ACQ, CS_LD, CS_ST, REL,
      DONE) = range(12)
@@ -1114,6 +1171,163 @@ class CuCohortLockModel:
                 any(cg[i][0] != ct[i] for i in range(self.NG)):
             return "a lock level not released at the end"
         return None
+
+
+class CuCohortEarlyGrantModel(CuCohortLockModel):
+    """The CU-cohort lock's hand-over of plain (fenced) sections: a pass within the CU does
+    not wait for the section's stores.
+
+    As CuCohortLockModel, but two data words (an agent's place among its CU's agents, modulo
+    2, says which one it increments; every holder loads both), and a store stays in flight
+    until its agent waits for it: loads of the same CU see it (they follow it through the
+    CU's queue), the L2 and so every other CU do not.  Stores of two agents may land in
+    either order.  Unlock: decide on the pass, by the announcement as of the entry or else as
+    of now; if passing, grant within the group; wait for the own store (it lands in the L2);
+    wait until the group's completion count has reached one's ticket, that is until every
+    earlier holder's store has landed; if not passing, hand the XCD lock on; store the count
+    ticket + 1; if not passing, grant session 0.
+    mutant 'no_count_wait': the holder that hands the XCD lock on does not wait for the
+    count;
+    mutant 'count_before_store': a holder that passed counts itself before its store landed;
+    mutant 'record_after_grant': the record is written behind the first grant that refers to
+    it;
+    'no_acquire', 'group_by_xcd' and 'no_waiter_check' as in CuCohortLockModel."""
+
+    (DRAW_C, ANN, POLL_C, DRAW_X, POLL_X, DRAW_G, POLL_G, ACQ, CS_LD, CS_ST, GRANT, WAIT,
+     COUNT, HAND, DONE) = range(15)
+
+    def __init__(self, placement: tuple, ops: int = 2, B: int = 2, mutant: str | None = None):
+        super().__init__(placement, ops, B, mutant)
+        # words: at most two agents per CU, so that each has at most one store in flight
+        # to a word of its own
+        self.word = tuple(sum(c == cu for _, c in self.pl[:a]) for a, (_, cu) in
+                          enumerate(self.pl))
+        assert max(self.word) <= 1
+
+    # shared = CuCohortLockModel's with l1 (NC of (value or None) x 2),
+    #          l2 (X of ((value, dirty) or None) x 2), mem (2), then
+    #          flight (n: value or None), cnt (NG)
+    # local  = (pc, j, tc, kc, tx, kx, tmp, ps)
+    def init(self):
+        X, NG, NC = self.X, self.NG, self.NC
+        sh = (0, 0, (0,) * X, ((0, 0),) * X, (0,) * NG, (0,) * NG, ((0, 0),) * NG,
+              ((0, 0),) * NG, ((None, None),) * NC, ((None, None),) * X, (0, 0), 0, 0, None,
+              (None,) * self.n, (0,) * NG)
+        return sh, tuple((self.DRAW_C, 0, 0, 0, 0, 0, 0, 0) for _ in range(self.n))
+
+    def step(self, a, sh, lo):
+        (gt, gturn, xt, xg, ct, ann, cg, rec, l1, l2, mem, inside, done_cs, bad, flight,
+         cnt) = sh
+        pc, j, tc, kc, tx, kx, tmp, ps = lo
+        x, cu = self.pl[a]
+        g, word = self.grp[a], self.word[a]
+        S = self._set
+
+        def out(pc2, **kw):
+            v = dict(gt=gt, gturn=gturn, xt=xt, xg=xg, ct=ct, ann=ann, cg=cg, rec=rec, l1=l1,
+                     l2=l2, mem=mem, inside=inside, done_cs=done_cs, bad=bad, flight=flight,
+                     cnt=cnt, tc=tc, kc=kc, tx=tx, kx=kx, tmp=tmp, ps=ps, j=j)
+            v.update(kw)
+            lo2 = (pc2, v["j"], v["tc"], v["kc"], v["tx"], v["kx"], v["tmp"], v["ps"])
+            if pc2 in (self.DRAW_C, self.DONE):
+                lo2 = (pc2, v["j"], 0, 0, 0, 0, 0, 0)  # nothing is kept between operations
+            return ((v["gt"], v["gturn"], v["xt"], v["xg"], v["ct"], v["ann"], v["cg"],
+                     v["rec"], v["l1"], v["l2"], v["mem"], v["inside"], v["done_cs"], v["bad"],
+                     v["flight"], v["cnt"]), lo2)
+
+        nxt = self.DRAW_C if j + 1 < self.ops else self.DONE
+        if pc == self.DRAW_C:
+            return out(self.ANN, ct=S(ct, g, ct[g] + 1), tc=ct[g])
+        if pc == self.ANN:
+            return out(self.POLL_C, ann=S(ann, g, tc + 1))
+        if pc == self.POLL_C:
+            turn, sess = cg[g]
+            if turn != tc:
+                return sh, lo
+            ps = int(ann[g] > tc + 1 and sess + 1 < self.B)
+            if sess > 0:
+                return out(self.CS_LD, kc=sess, tx=rec[g][0], kx=rec[g][1], ps=ps)
+            return out(self.DRAW_X, kc=0, ps=ps)
+        if pc == self.DRAW_X:
+            return out(self.POLL_X, xt=S(xt, x, xt[x] + 1), tx=xt[x])
+        if pc == self.POLL_X:
+            turn, sess = xg[x]
+            if turn != tx:
+                return sh, lo
+            return out(self.ACQ if sess > 0 else self.DRAW_G, kx=sess)
+        if pc == self.DRAW_G:
+            return out(self.POLL_G, gt=gt + 1, tmp=gt)
+        if pc == self.POLL_G:
+            return out(self.ACQ, tmp=0) if gturn == tmp else (sh, lo)
+        if pc == self.ACQ:
+            if self.mutant != "no_acquire":
+                l1 = S(l1, cu, (None, None))
+                l2 = S(l2, x, tuple(w if w is not None and w[1] else None for w in l2[x]))
+            if self.mutant != "record_after_grant":
+                rec = S(rec, g, (tx, kx))
+            return out(self.CS_LD, l1=l1, l2=l2, rec=rec)
+        if pc == self.CS_LD:
+            seen = []
+            for w in range(2):
+                v = next((flight[b] for b in range(self.n) if self.pl[b] == (x, cu) and
+                          self.word[b] == w and flight[b] is not None), l1[cu][w])
+                if v is None:
+                    if l2[x][w] is None:
+                        l2 = S(l2, x, S(l2[x], w, (mem[w], False)))
+                    v = l2[x][w][0]
+                    l1 = S(l1, cu, S(l1[cu], w, v))
+                seen.append(v)
+            if inside:
+                bad = bad or "two holders inside"
+            elif sum(seen) != done_cs:
+                bad = bad or f"stale read: {seen} after {done_cs} sections"
+            return out(self.CS_ST, l1=l1, l2=l2, tmp=seen[word], inside=inside + 1, bad=bad)
+        if pc == self.CS_ST:
+            if inside > 1:
+                bad = bad or "two holders inside"
+            return out(self.GRANT, l1=S(l1, cu, S(l1[cu], word, tmp + 1)),
+                       flight=S(flight, a, tmp + 1), inside=inside - 1, done_cs=done_cs + 1,
+                       bad=bad, tmp=0)
+        if pc == self.GRANT:
+            ps = int(kc + 1 < self.B and (ps or ann[g] > tc + 1 or
+                                          self.mutant == "no_waiter_check"))
+            if ps:
+                cg = S(cg, g, (tc + 1, kc + 1))
+            early = ps and self.mutant == "count_before_store"
+            return out(self.COUNT if early else self.WAIT, cg=cg, ps=ps)
+        if pc == self.WAIT:  # the own store lands
+            l2 = S(l2, x, S(l2[x], word, (flight[a], True)))
+            if self.mutant == "record_after_grant" and kc == 0:
+                rec = S(rec, g, (tx, kx))
+            if self.mutant == "count_before_store" and ps:
+                return out(nxt, l2=l2, flight=S(flight, a, None), j=j + 1)
+            return out(self.COUNT, l2=l2, rec=rec, flight=S(flight, a, None))
+        if pc == self.COUNT:
+            if cnt[g] != tc and (ps or self.mutant != "no_count_wait"):
+                return sh, lo
+            if ps:
+                cnt = S(cnt, g, tc + 1)
+                if self.mutant == "count_before_store":
+                    return out(self.WAIT, cnt=cnt)
+                return out(nxt, cnt=cnt, j=j + 1)
+            if xt[x] > tx + 1 and kx + 1 < self.B:
+                xg = S(xg, x, (tx + 1, kx + 1))
+            else:
+                for w in range(2):
+                    if l2[x][w] is not None and l2[x][w][1]:
+                        mem = S(mem, w, l2[x][w][0])
+                        l2 = S(l2, x, S(l2[x], w, (mem[w], False)))
+                gturn = gturn + 1
+                xg = S(xg, x, (tx + 1, 0))
+            return out(self.HAND, xg=xg, l2=l2, mem=mem, gturn=gturn)
+        if pc == self.HAND:
+            return out(nxt, cnt=S(cnt, g, tc + 1), cg=S(cg, g, (tc + 1, 0)), j=j + 1)
+        raise AssertionError(pc)
+
+    def final_check(self, sh, los):
+        if any(v is not None for v in sh[14]) or sh[15] != sh[4]:
+            return "stores in flight or holders uncounted at the end"
+        return super().final_check(sh, los)
 
 
 class XcdChainSemModel:

@@ -459,7 +459,9 @@ int or_barrier_threaded(int kind, uint32_t seed, uint32_t N, uint32_t R, uint32_
 // queue of per-agent nodes: lock exchanges the tail with one's node and, behind a
 // predecessor, links in and waits on one's own node; unlock hands over to the successor
 // or, when none has linked in, swings the tail back to empty with a compare-and-swap),
-// 10 CU-cohort lock (kind 8 with a ticket lock per CU group in front of each cohort's).
+// 10 CU-cohort lock (kind 8 with a ticket lock per CU group in front of each cohort's; a
+// hand-over within the group comes before the holder's completion is counted, and the
+// cohort lock leaves the group only once every holder before has been).
 // Workload: see or_mutex_closed.  An owner word checks mutual exclusion inside every
 // critical section.  Returns 0, or -2 on a mutual-exclusion violation.
 int or_mutex_threaded(int kind, uint32_t seed, uint32_t nwg, uint64_t total, uint32_t L,
@@ -492,14 +494,15 @@ int or_mutex_threaded(int kind, uint32_t seed, uint32_t nwg, uint64_t total, uin
   // kind 10 (CU cohort): agent b of cohort b mod kCoh sits in CU group (b / kCoh) mod kCu
   // of it; per lock and CU group a ticket counter, a grant word (CU turn | CU session <<
   // 32), the record of the cohort lock the group's session holds (what kind 8's lock
-  // returned) and the announcement of the tickets drawn (a lower bound, stores in any
-  // order); at most kPasses holders of a group in a row.  cu_hold keeps each agent's CU
-  // ticket | CU session << 32 while it holds a lock.
+  // returned), the announcement of the tickets drawn (a lower bound, stores in any order)
+  // and the count of holders complete, in ticket order; at most kPasses holders of a group
+  // in a row.  cu_hold keeps each agent's CU ticket | CU session << 32 while it holds a
+  // lock, with bit 63 set if a later ticket was announced when it entered.
   constexpr uint32_t kCu = 4;
   const size_t ncu = kind == 10 ? (size_t)L * kCoh * kCu : 0;
-  std::vector<Word> cut(ncu), cann(ncu);
+  std::vector<Word> cut(ncu), cann(ncu), cdone(ncu);
   std::vector<std::atomic<uint64_t>> cgrant(ncu), crec(ncu);
-  for (size_t i = 0; i < ncu; ++i) cut[i] = 0, cann[i] = 0, cgrant[i] = 0, crec[i] = 0;
+  for (size_t i = 0; i < ncu; ++i) cut[i] = 0, cann[i] = 0, cdone[i] = 0, cgrant[i] = 0, crec[i] = 0;
   std::vector<uint64_t> cu_hold(kind == 10 ? nwg : 0);
 
   // kind 8's two levels: the cohort's local ticket lock, then the global one unless the
@@ -604,7 +607,8 @@ int or_mutex_threaded(int kind, uint32_t seed, uint32_t nwg, uint64_t total, uin
         uint64_t v;
         while ((uint32_t)(v = cgrant[u].load(std::memory_order_acquire)) != tc) relax();
         const uint32_t kc = (uint32_t)(v >> 32);
-        cu_hold[b] = ((uint64_t)kc << 32) | tc;
+        const bool pass = kc + 1 < kPasses && (int32_t)(cann[u].load() - (tc + 1)) > 0;
+        cu_hold[b] = ((uint64_t)pass << 63) | ((uint64_t)kc << 32) | tc;
         if (kc > 0) return crec[u].load(std::memory_order_relaxed);
         const uint64_t held = cohort_lock(l, b);
         crec[u].store(held, std::memory_order_relaxed);  // for the group's later holders
@@ -640,15 +644,19 @@ int or_mutex_threaded(int kind, uint32_t seed, uint32_t nwg, uint64_t total, uin
       return;
     }
     if (kind == 10) {
+      // Pass within the group by the announcement as of the entry or else as of now; then
+      // wait for the group's earlier holders to have counted themselves complete, hand the
+      // cohort lock on if not passing, count oneself, grant session 0 if not passing.
       const size_t u = cu_of(l, b);
-      const uint32_t tc = (uint32_t)cu_hold[b], kc = (uint32_t)(cu_hold[b] >> 32) + 1;
-      const bool waiter = (int32_t)(cann[u].load(std::memory_order_relaxed) - (tc + 1)) > 0;
-      if (waiter && kc < kPasses) {  // the group's next holder keeps the cohort lock
-        cgrant[u].store(((uint64_t)kc << 32) | (tc + 1), std::memory_order_release);
-      } else {
-        cohort_unlock(l, b, held);
-        cgrant[u].store(tc + 1, std::memory_order_release);  // session 0
-      }
+      const uint32_t tc = (uint32_t)cu_hold[b], kc = ((uint32_t)(cu_hold[b] >> 32) & 0xFF) + 1;
+      bool pass = cu_hold[b] >> 63;
+      if (!pass && kc < kPasses)
+        pass = (int32_t)(cann[u].load(std::memory_order_relaxed) - (tc + 1)) > 0;
+      if (pass) cgrant[u].store(((uint64_t)kc << 32) | (tc + 1), std::memory_order_release);
+      while (cdone[u].load(std::memory_order_acquire) != tc) relax();
+      if (!pass) cohort_unlock(l, b, held);
+      cdone[u].store(tc + 1, std::memory_order_release);
+      if (!pass) cgrant[u].store(tc + 1, std::memory_order_release);  // session 0
       return;
     }
     if (kind == 3 || kind == 7) {
