@@ -15,6 +15,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libsp.so")
+DEVICE_TESTS = os.path.join(ROOT, "tests", "device")
+DEVICE_TESTS_LIB = os.path.join(DEVICE_TESTS, "libsp_device_tests.so")
 
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -64,6 +66,20 @@ def build(verbose: bool = False, save_temps: bool = False) -> str:
                    check=True)
     os.replace(tmp, LIB)
     return LIB
+
+
+def build_device_tests() -> str:
+    """The kernels of tests/device, which use the device headers as a caller's program does."""
+    srcs = sorted(os.path.join(DEVICE_TESTS, f) for f in os.listdir(DEVICE_TESTS)
+                  if f.endswith(".hip"))
+    tmp = DEVICE_TESTS_LIB + ".tmp"
+    p = subprocess.run([HIPCC, *CFLAGS, "-shared", *srcs, "-o", tmp], stdout=subprocess.PIPE,
+                       stderr=subprocess.STDOUT, text=True)
+    if p.returncode != 0:
+        print(p.stdout, file=sys.stderr)
+        raise RuntimeError("hipcc failed for the device tests")
+    os.replace(tmp, DEVICE_TESTS_LIB)
+    return DEVICE_TESTS_LIB
 
 
 if __name__ == "__main__":
