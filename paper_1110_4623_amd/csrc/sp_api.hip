@@ -97,6 +97,7 @@ int normalize(const sp_ctx* ctx, const sp_params* in, sp_params* out) {
 }
 
 int reset(sp_ctx* ctx, const Resets& z, hipStream_t s) {
+  if (z.n > Resets::kMax) return SP_E_INVAL;
   uint64_t most = 0;
   for (uint32_t k = 0; k < z.n; ++k) most = std::max(most, z.r[k].words);
   if (most == 0) return SP_OK;

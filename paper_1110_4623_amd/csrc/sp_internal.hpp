@@ -104,7 +104,8 @@ inline sp::BackoffCfg backoff_cfg(const sp_params& p, uint32_t* private_word) {
 }
 
 // Up to kMax ranges of uint32 words set by one kernel (no memset nodes, so launches stay
-// capturable): what a run has to reset costs one launch, not one per array.
+// capturable): what a run has to reset costs one launch, not one per array.  A range too many
+// is counted but not kept, and the reset refuses the list.
 struct Resets {
   static constexpr uint32_t kMax = 8;
   struct Range {
@@ -114,7 +115,9 @@ struct Resets {
   } r[kMax];
   uint32_t n = 0;
   void add(void* p, uint64_t words, uint32_t value = 0) {
-    if (words) r[n++] = Range{static_cast<uint32_t*>(p), words, value};
+    if (!words) return;
+    if (n < kMax) r[n] = Range{static_cast<uint32_t*>(p), words, value};
+    ++n;
   }
 };
 int reset(sp_ctx* ctx, const Resets& z, hipStream_t s);

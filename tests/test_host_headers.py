@@ -38,3 +38,18 @@ def test_cu_cohort_unlock_ends_with_the_watchdog(unlock_watchdog, how):
     its count ends, with a control block or without, and cond_wait reports the end."""
     p = subprocess.run([str(unlock_watchdog), how], capture_output=True, text=True, timeout=20)
     assert (p.returncode, p.stdout) == (0, "ended\n"), (p.returncode, p.stdout, p.stderr)
+
+
+def test_reset_list_refuses_one_range_too_many(tmp_path):
+    from paper_1110_4623_amd import _native as N
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if shutil.which(hipcc) is None:
+        pytest.skip("hipcc not available")
+    exe = tmp_path / "resets"
+    subprocess.check_call([hipcc, "--cuda-host-only", "-x", "hip", "-std=c++17", "-O1", "-w",
+                           "-I", os.path.join(ROOT, "include"), "-I",
+                           os.path.join(ROOT, "paper_1110_4623_amd", "csrc"),
+                           os.path.join(HOST, "resets.cpp"), "-x", "none", N.LIB_PATH,
+                           "-Wl,-rpath," + os.path.dirname(N.LIB_PATH), "-o", str(exe)])
+    p = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert (p.returncode, p.stdout) == (0, "refused\n"), (p.returncode, p.stdout, p.stderr)
