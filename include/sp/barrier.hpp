@@ -141,8 +141,7 @@ __device__ __forceinline__ bool counter_arrive_wait(const BarrierState& s, uint3
 // Master side of a flag scan: every lane checks flags i = lane, lane + lanes, ... of
 // `n` flags (skipping index `skip`) and all of a lane's flags are loaded together each
 // poll, so a scan costs one memory round trip rather than one per flag.  `lanes` is the
-// workgroup size (the per-XCD barrier passes the value it saved in round 0: reading
-// blockDim.x is a load from the dispatch packet).
+// workgroup size.
 __device__ __forceinline__ int scan_flags(const uint32_t* flags, uint32_t fs, uint32_t n,
                                           uint32_t skip, uint32_t stamp, Wait& w,
                                           uint32_t lanes) {

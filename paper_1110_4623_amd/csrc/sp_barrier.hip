@@ -48,11 +48,10 @@ struct SlotLayout {
 // values 1.86 -> 1.38; 1024 of 256 lanes 4.76 -> 4.43, 2.89 -> 2.24; 2048 of 256 lanes
 // 5.13 -> 4.81, 3.22 -> 2.68.
 SlotLayout slot_layout(uint32_t kind, uint32_t nwg, uint32_t xcds, bool coherent) {
-  const uint32_t most = 1u << 16;  // (more workgroups than can run: no room for lines)
   SlotLayout at;
   const bool by_xcd = coherent || kind == SP_BARRIER_XCD || nwg <= 64;
   at.blocks = by_xcd ? std::max<uint32_t>(1, xcds) : 1;
-  at.step = coherent && nwg <= most ? 32 : 1;
+  at.step = coherent ? 32 : 1;  // (2 x 8 MiB for the 65536 workgroups that create takes)
   at.block_words = ((nwg + at.blocks - 1) / at.blocks * at.step + 31) / 32 * 32;
   return at;
 }
