@@ -469,8 +469,15 @@ __device__ __forceinline__ bool barrier_wait(const BarrierState& s, uint32_t rou
                                              const Ctl& ctl) {
   __shared__ uint32_t s_ok;
   const uint32_t stamp = round + 1;
-  // (the per-XCD barrier's workgroups arrive without a release fence)
-  stores_complete_before_release(KIND != SP_BARRIER_XCD && s.fenced);
+  // The leader's wavefront skips this wait ahead of its release fence only where that is
+  // faster: a central barrier of fewer than 512 workgroups, whose arrivals are one chain (us
+  // per round with the wait / without, one wavefront per workgroup: 64 workgroups 3.99 / 3.54,
+  // 256 8.5 / 8.3, 384 21.5 / 20.3, 512 28.7 / 30.5, 768 40.0 / 44.9, 1024 47.7 / 55.9).
+  // Where many workgroups write back side by side, a writeback that comes upon a store on its
+  // way takes longer: tree, 512 / 2048 workgroups 10.9 / 34.3 against 11.2 / 36.4; split
+  // counter, 1024 24.1 against 26.0; flags, 512 12.2 against 13.0.  The per-XCD barrier's
+  // workgroups arrive without a release fence.
+  stores_complete_before_release(KIND == SP_BARRIER_CENTRAL && s.fenced && s.nwg < 512);
   if constexpr (KIND == SP_BARRIER_FLAG) {
     return detail::flag_wait(s, stamp, ctl);
   } else if constexpr (KIND == SP_BARRIER_XCD) {
