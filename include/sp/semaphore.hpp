@@ -360,8 +360,10 @@ __device__ bool sem_wait(const SemState& s, const Ctl& ctl, SemHold* hold = null
       Wait w(ctl, s.poll_sleep);
       const uint32_t t = add_relaxed(s.ticket, 1);
       uint32_t posts = ld_relaxed(s.turn);  // in flight with the ticket; a lower bound
-      if (!((int32_t)(posts + s.K - t) > 0))
-        ok = poll(w, [&] { return (int32_t)uniform(ld_relaxed(s.turn) + s.K - t) > 0; });
+      while (!((int32_t)(posts + s.K - t) > 0)) {
+        if (!(ok = w.tick())) break;
+        posts = ld_relaxed(s.turn);
+      }
     } else {
       Wait w(ctl, KIND == SP_SEM_SLEEP ? s.poll_sleep : 0);
       const uint32_t old = add_relaxed(s.count, 1);
@@ -388,9 +390,20 @@ __device__ bool sem_post(const SemState& s, const Ctl& ctl, const SemHold* hold 
     return true;
   }
   __shared__ uint32_t s_ok;
-  // these two hand units on within an XCD without a release fence
-  if constexpr (COMPLETE)
-    stores_complete_before_release(FENCED && KIND != SP_SEM_COHORT && KIND != SP_SEM_XCD_CHAIN);
+  if constexpr (COMPLETE) {
+    // The leader's wavefront skips the wait ahead of its release fence, except in the kinds
+    // that hand units on within an XCD without one, and in two that post to one word where
+    // many units end side by side: a writeback that comes upon stores on their way takes
+    // longer there.  ms per 2000 x min(K, 4) pairs on 512 workgroups, waiting / not:
+    // counters, K = 24 1.41 / 1.35, 32 0.94 / 1.22, 64 0.59 / 1.02, 256 0.54 / 0.87;
+    // sleeping, K = 128 0.57 / 0.83, 256 0.60 / 0.80.  Below, not waiting is faster for 64
+    // and 2048 workgroups too (counters, K = 4 4.03 / 3.77; sleeping, K = 32, 2048
+    // workgroups 1.59 / 1.53).
+    const bool wait = (KIND == SP_SEM_COUNTERS && s.K >= 32) ||
+                      (KIND == SP_SEM_SLEEP && s.K >= 128);
+    stores_complete_before_release(FENCED && KIND != SP_SEM_COHORT &&
+                                   KIND != SP_SEM_XCD_CHAIN && !wait);
+  }
   __syncthreads();
   if constexpr (KIND == SP_SEM_COHORT) {
     // Hand the unit on.  Algorithm 5's post: write back, then decrement count; if a waiter
