@@ -160,7 +160,9 @@ __device__ __forceinline__ void fence_release() {
 // Every wavefront's stores complete before the workgroup barrier that precedes a leader's
 // fence_release(); without that fence (`fenced` false) the leader's too.  The leader's own
 // wavefront need not wait with it: the fence writes back what the wavefront stored before it
-// and waits for both (the wait cost ~150 shader clocks of every hand-over).
+// and waits for both (the wait cost ~150 shader clocks of every hand-over).  Where many
+// workgroups write back side by side the wait is the faster way all the same: barrier_wait and
+// sem_post say where.
 __device__ __forceinline__ void stores_complete_before_release(bool fenced) {
   if (!fenced || __builtin_amdgcn_readfirstlane(threadIdx.x) >= 64) wave_stores_complete();
 }

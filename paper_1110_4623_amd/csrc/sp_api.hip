@@ -318,9 +318,9 @@ int sp_init(int device, sp_ctx** out) {
   ctx->defaults[1][0].kind = SP_MUTEX_SPIN_BACKOFF;
   ctx->defaults[1][0].p.backoff = SP_BACKOFF_PAPER;
   ctx->defaults[1][0].p.backoff_max = 8;
-  // CU-cohort lock (the XCD-cohort lock below two contenders per CU and lock): one lock
-  // 1.57 M/s at 2048 workgroups, 1.60 at 1024 (XCD-cohort lock 1.00, ticket 0.70); 16 locks
-  // at 2048 run the XCD-cohort lock, 17.1 M/s (array 11.2)
+  // CU-cohort lock (the XCD-cohort lock below 2.5 contenders per CU and lock, 5 for coherent
+  // sections): one lock 1.57 M/s at 2048 workgroups, 1.62 at 1024 (XCD-cohort lock 1.02,
+  // ticket 0.70); 16 locks at 2048 run the XCD-cohort lock, 17 M/s (array 11.2)
   ctx->defaults[1][1].kind = SP_MUTEX_CU_COHORT;
   ctx->defaults[1][1].p.poll_sleep = 0;
   ctx->defaults[1][1].p.cohort_passes = 64;

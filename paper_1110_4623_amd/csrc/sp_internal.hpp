@@ -190,21 +190,26 @@ struct DeviceScratch {
 };
 
 inline uint32_t bucket_of(uint32_t contenders) { return contenders >= 64 ? 1u : 0u; }
-// Barriers: every workgroup is a contender.  The central counter is the faster default up
-// to 32 workgroups and the per-XCD barrier from 48 on (1.75 / 2.39 / 3.88 against 2.72 /
-// 2.72 / 2.85 us per round at 16 / 32 / 48, 256 lanes), so the high bucket starts at 40.
+// Barriers: every workgroup is a contender.  Us per round, central counter / per-XCD, 256
+// lanes: plain data, 16 workgroups 1.69 / 2.35, 32 2.35 / 2.34, 40 2.65 / 2.36, 48 2.98 /
+// 2.42, 64 3.50 / 2.51; agent-scope data 1.23 / 1.96, 1.53 / 1.95, 1.53 / 1.96, 1.62 / 1.96,
+// 1.78 / 2.00.  The two meet at 32 for plain data and above 64 for agent-scope data; one line
+// serves both, and the high bucket starts at 40.
 inline uint32_t barrier_bucket_of(uint32_t nwg) { return nwg >= 40 ? 1u : 0u; }
 // A default mutex whose bucket names the CU-cohort lock runs it only where a lock has
 // enough contenders per CU; below that few hand-overs stay within a CU and the XCD-cohort
 // lock is faster.  M acquisitions/s, CU-cohort / XCD-cohort, 16 words: plain data, one lock,
-// 512 workgroups 0.93 / 1.02, 640 1.15 / 1.02, 1024 1.59 / 1.02; 2048 workgroups on 2
-// locks 2.52 / 2.10, 3 3.41 / 3.21, 4 4.26 / 4.25, 6 5.88 / 6.36: from 2.5 per CU and lock.
-// Coherent data, whose sections go to memory whatever the hand-over: one lock, 1024
-// workgroups 1.11 / 1.03; 2048 on 2 locks 2.08 / 2.09, on 3 3.02 / 3.16: from 5.
+// 512 workgroups 0.93 / 1.02, 640 1.17 / 1.02, 1024 1.66 / 1.02; 2048 workgroups on 2
+// locks 2.57 / 2.05, 3 3.53 / 3.15, 4 4.43 / 4.23, 8 7.81 / 8.56: from 2.5 per CU and lock
+// (2 per CU go either way).  Coherent data, whose sections go to memory
+// whatever the hand-over: 2048 on one lock 1.12 / 1.03, on 2 2.11 / 2.06, on 3 3.07 / 3.11,
+// on 4 4.03 / 4.16: from 5, where the gain is sure.
 inline bool cu_cohort_pays(uint64_t nwg, uint64_t nlocks, uint64_t cu_count, bool coherent) {
   return 2 * nwg >= (coherent ? 10 : 5) * nlocks * cu_count;
 }
-// The K = 1 semaphore's line between one chain and the CU-cohort lock.
+// The K = 1 semaphore's line between one chain and the CU-cohort lock.  M pairs/s, lock /
+// chain, holds U[0, 2000] clocks: plain data, 256 workgroups 0.61 / 0.74, 384 0.74 / 0.72, 512
+// 0.84 / 0.72, 2048 0.99 / 0.66; coherent 384 0.89 / 0.93, 512 0.96 / 0.91, 2048 0.95 / 0.84.
 inline bool cu_lock_pays(uint64_t nwg, uint64_t cu_count) { return nwg >= 2 * cu_count; }
 // A default mutex whose low bucket is the library's own (the spin lock with the paper's
 // backoff) runs the XCD-cohort lock where a lock has enough contenders that some of them

@@ -136,8 +136,9 @@ int sp_mutex_create(sp_ctx* ctx, uint32_t kind, uint32_t nlocks, uint32_t words_
   for (int b = 0; b < 2 && kind == SP_MUTEX_DEFAULT; ++b) {
     const sp_default_entry& d = ctx->defaults[1][b];
     uint32_t dk = d.kind;
-    // the CU-cohort lock runs only with two contenders per CU and lock, which a grid of
-    // at most maxThreadsPerMultiProcessor / 64 workgroups per CU may not reach
+    // the CU-cohort lock runs only with 2.5 contenders per CU and lock (5 for coherent
+    // sections), which a grid of at most maxThreadsPerMultiProcessor / 64 workgroups per CU
+    // may not reach
     const uint64_t max_wg = (uint64_t)ctx->cu_count * (ctx->prop.maxThreadsPerMultiProcessor / 64);
     if (dk == SP_MUTEX_CU_COHORT &&
         !spi::cu_cohort_pays(max_wg, nlocks, ctx->cu_count, q.coherent_cs != 0))
